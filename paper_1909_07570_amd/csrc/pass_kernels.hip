@@ -35,8 +35,71 @@ static __device__ inline f4 p_mfma_f32(float a, float b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
+// Ragged variants (RAG below) of the two row-streaming kernels and of the FP32 earlier-mode
+// kernel: X, the output and X's rows may start at any element.  A 16-byte chunk is then
+// loaded with element alignment (the target's unaligned access mode: one request, split by
+// the memory pipeline only where it crosses a 64-byte block), and the last chunk of a row
+// that is no whole number of chunks is read from the row's last whole 16 bytes, so no load
+// leaves X.  They replace the general kernel there, which walks the contracted index
+// serially and re-reads X once per four ranks: 301 x 250 x 187 FP32, 187 us per pass.
+typedef f4 f4_el __attribute__((aligned(4)));
+typedef u4 u4_e4 __attribute__((aligned(4)));
+typedef u4 u4_e2 __attribute__((aligned(2)));
+template <bool BF, bool RAG>
+static __device__ inline u4 p_load_nt(const void *p) {
+  if (!RAG) return __builtin_nontemporal_load(reinterpret_cast<const u4 *>(p));
+  if (BF) return *reinterpret_cast<const u4_e2 *>(p);
+  return *reinterpret_cast<const u4_e4 *>(p);
+}
+
+// Three bf16 parts of a float by truncation: their sum is the float exactly (8 bits each; a
+// part below the bf16 range is lost with it).  The ragged BF16 passes apply the factor so, as
+// the general kernel before them applied it in full; an infinite or NaN entry keeps to the
+// first part.
+static __device__ inline void p_split3(float a, uint16_t *h, uint16_t *m, uint16_t *l) {
+  const uint32_t u = __float_as_uint(a);
+  const bool fin = (u & 0x7f800000u) != 0x7f800000u;
+  const bool nan = (u & 0x7fffffffu) > 0x7f800000u;
+  *h = (uint16_t)((u >> 16) | (nan ? 0x40u : 0u));
+  const float r1 = fin ? a - __uint_as_float(u & 0xffff0000u) : 0.f;
+  const uint32_t u1 = __float_as_uint(r1);
+  const float r2 = r1 - __uint_as_float(u1 & 0xffff0000u);
+  *m = (uint16_t)(u1 >> 16);
+  *l = (uint16_t)(__float_as_uint(r2) >> 16);
+}
+
+// v shifted towards its first byte by `bits` (a multiple of 16, < 128), zeros shifted in.
+static __device__ inline u4 p_shift_down(u4 v, int bits) {
+  const int dw = bits >> 5;
+  u4 w = v;
+  if (dw == 1) w = u4{v[1], v[2], v[3], 0u};
+  if (dw == 2) w = u4{v[2], v[3], 0u, 0u};
+  if (dw == 3) w = u4{v[3], 0u, 0u, 0u};
+  if (bits & 16)
+    w = u4{(w[0] >> 16) | (w[1] << 16), (w[1] >> 16) | (w[2] << 16), (w[2] >> 16) | (w[3] << 16), w[3] >> 16};
+  return w;
+}
+
 constexpr int kPassThreads = 256;
 constexpr int kUnitChunks = 16;  // 16-byte loads per lane per work unit
+
+// Columns q .. q + 3 of an output row in the ragged earlier-mode kernels.  A loader lane's chunk
+// is EPC columns of X from q8 = q rounded down to its chunk.  Where that chunk reaches past the
+// row's end it was read (and its columns computed) from the row's last whole 16 bytes, so `val`
+// then stands for columns qt .. qt + 3 with qt = Q - EPC + (q - q8), and only those from q8 on
+// are stored: the ones before belong to the chunk before.
+static __device__ inline void p_store_ragged(float *row, int64_t q, int64_t q8, int EPC, int64_t Q, f4 val, int acc) {
+  if (q8 + EPC <= Q) {
+    f4_el *o = reinterpret_cast<f4_el *>(row + q);
+    if (acc) val += *o;  // a later chunk of the contracted index
+    *o = val;
+  } else if (q8 < Q) {
+    const int64_t qt = Q - EPC + (q - q8);
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if (qt + c >= q8) row[qt + c] = acc ? row[qt + c] + val[c] : val[c];
+  }
+}
 
 // =====================================================================================
 // Last-mode contraction.  A work unit is 16 rows x KU k-values: lane (li = lane%16,
@@ -188,7 +251,7 @@ constexpr int kMidWaves = 8;
 constexpr int kMidDepth = 1;
 constexpr int kMidDepthF32 = 1;  // steps in flight per wave, FP32 X (one measured fastest, as for bf16)
 
-template <int RT, bool HS>
+template <int RT, bool HS, bool RAG>
 __global__ __launch_bounds__(64 * kMidWaves) __attribute__((amdgpu_waves_per_eu(RT == 1 ? 4 : 1))) void ttm_mid_lds_k(const uint16_t *__restrict__ X,
                                                                int64_t P, int N, int64_t Q,
                                                                const float *__restrict__ F,
@@ -207,7 +270,8 @@ __global__ __launch_bounds__(64 * kMidWaves) __attribute__((amdgpu_waves_per_eu(
   const int64_t qt = (Q + 127) >> 7;
   const int64_t ntile = P * qt;
   const int nsteps = Np >> 5;
-  float *stg = reinterpret_cast<float *>(lds_b + 2 * RP * NS * 2) + wave * (R * (HS ? 64 : 128));
+  uint16_t *lo2 = lo + RP * NS;  // RAG only
+  float *stg = reinterpret_cast<float *>(lds_b + (RAG ? 3 : 2) * RP * NS * 2) + wave * (R * (HS ? 64 : 128));
   u4 v[kMidDepth][8];
   const uint16_t *xp = X;  // lane's column of the current tile
   int nlim = 0;            // last row a load may touch (0: one line, for loads past the work)
@@ -215,14 +279,14 @@ __global__ __launch_bounds__(64 * kMidWaves) __attribute__((amdgpu_waves_per_eu(
     const int64_t p = t / qt;
     const int64_t q0 = (t - p * qt) * 128;
     const int64_t qa = q0 + 8 * li;
-    xp = X + p * ldp + (qa < Q ? qa : Q - 8);
+    xp = X + p * ldp + ((RAG ? qa + 8 <= Q : qa < Q) ? qa : Q - 8);
     nlim = N - 1;
   };
   auto load = [&](u4 (&vv)[8], int s) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const int n = min(32 * s + 8 * lg + j, nlim);
-      vv[j] = __builtin_nontemporal_load(reinterpret_cast<const u4 *>(xp + (int64_t)n * Q));
+      vv[j] = p_load_nt<true, RAG>(xp + (int64_t)n * Q);
     }
   };
   int64_t t = (int64_t)blockIdx.x * kMidWaves + wave;
@@ -249,6 +313,16 @@ __global__ __launch_bounds__(64 * kMidWaves) __attribute__((amdgpu_waves_per_eu(
         const int n = e / RP, r = e - (e / RP) * RP;
         const bool ok = e < total && n < N && r < R;
         const float a = ok ? fv[u] : 0.f;  // masked where the value is awaited
+        if (RAG) {
+          uint16_t h, m, l;
+          p_split3(a, &h, &m, &l);
+          if (e < total) {
+            hi[r * NS + n] = h;
+            lo[r * NS + n] = m;
+            lo2[r * NS + n] = l;
+          }
+          continue;
+        }
         const uint16_t h = p_f2bf(a);
         if (e < total) {
           hi[r * NS + n] = h;
@@ -267,12 +341,13 @@ __global__ __launch_bounds__(64 * kMidWaves) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
       for (int nt = 0; nt < RT; ++nt) acc[c][nt] = f4{0.f, 0.f, 0.f, 0.f};
     auto step = [&](u4 (&vv)[8], int s) {
-      u4 bh[RT], bl[RT];
+      u4 bh[RT], bl[RT], bm[RT];
 #pragma unroll
       for (int nt = 0; nt < RT; ++nt) {
         const int off = (nt * 16 + li) * NS + s * 32 + 8 * lg;
         bh[nt] = *reinterpret_cast<const u4 *>(hi + off);
         bl[nt] = *reinterpret_cast<const u4 *>(lo + off);
+        if (RAG) bm[nt] = *reinterpret_cast<const u4 *>(lo2 + off);
       }
 #pragma unroll
       for (int c = 0; c < 8; ++c) {
@@ -286,6 +361,7 @@ __global__ __launch_bounds__(64 * kMidWaves) __attribute__((amdgpu_waves_per_eu(
         for (int nt = 0; nt < RT; ++nt) {
           acc[c][nt] = p_mfma_bf16(op, bh[nt], acc[c][nt]);
           acc[c][nt] = p_mfma_bf16(op, bl[nt], acc[c][nt]);
+          if (RAG) acc[c][nt] = p_mfma_bf16(op, bm[nt], acc[c][nt]);
         }
       }
       load(vv, s + kMidDepth);
@@ -328,7 +404,10 @@ __global__ __launch_bounds__(64 * kMidWaves) __attribute__((amdgpu_waves_per_eu(
       for (int rr = 0; rr < R; rr += 2) {
         const int r = rr + (lane >> 5);
         const int qq = (lane & 31) * 4;
-        if (r < R && q0 + qq < Q) {
+        if (RAG && r < R) {
+          const f4 val = *reinterpret_cast<const f4 *>(stg + r * 128 + qq);
+          p_store_ragged(out + (p * R + r) * Q, q0 + qq, q0 + (qq & ~7), 8, Q, val, acc_out);
+        } else if (r < R && q0 + qq < Q) {
           f4 *o = reinterpret_cast<f4 *>(out + (p * R + r) * Q + q0 + qq);
           f4 val = *reinterpret_cast<const f4 *>(stg + r * 128 + qq);
           if (acc_out) {
@@ -366,7 +445,10 @@ __global__ __launch_bounds__(64 * kMidWaves) __attribute__((amdgpu_waves_per_eu(
           const int r = rr + (lane >> 4);
           const int qq = (lane & 15) * 4;
           const int64_t qc = q0 + 64 * h + qq;
-          if (r < R && qc < Q) {
+          if (RAG && r < R) {
+            const f4 val = *reinterpret_cast<const f4 *>(stg + r * 64 + qq);
+            p_store_ragged(out + (p * R + r) * Q, qc, qc - (qq & 7), 8, Q, val, acc_out);
+          } else if (r < R && qc < Q) {
             f4 *o = reinterpret_cast<f4 *>(out + (p * R + r) * Q + qc);
             f4 val = *reinterpret_cast<const f4 *>(stg + r * 64 + qq);
             if (acc_out) {
@@ -392,7 +474,7 @@ __global__ __launch_bounds__(64 * kMidWaves) __attribute__((amdgpu_waves_per_eu(
 // (li, lg) ends up holding, for output column r = 16 nt + li and i = 0..3, the four
 // adjacent columns q0 + 16 lg + 4 i + (0..3) of each accumulator set c.
 // =====================================================================================
-template <int RT, int DEPTH>
+template <int RT, int DEPTH, bool RAG>
 __global__ __launch_bounds__(64 * kMidWaves) __attribute__((amdgpu_waves_per_eu(4))) void ttm_mid_lds_f32_k(const float *__restrict__ X,
                                                                    int64_t P, int N, int64_t Q,
                                                                    const float *__restrict__ F,
@@ -419,14 +501,14 @@ __global__ __launch_bounds__(64 * kMidWaves) __attribute__((amdgpu_waves_per_eu(
     const int64_t p = t / qt;
     const int64_t q0 = (t - p * qt) * 64;
     const int64_t qa = q0 + 4 * li;
-    xp = X + p * ldp + (qa < Q ? qa : Q - 4);
+    xp = X + p * ldp + ((RAG ? qa + 4 <= Q : qa < Q) ? qa : Q - 4);
     nlim = N - 1;
   };
   auto load = [&](u4 (&vv)[8], int s) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const int n = min(32 * s + 8 * lg + j, nlim);
-      vv[j] = __builtin_nontemporal_load(reinterpret_cast<const u4 *>(xp + (int64_t)n * Q));
+      vv[j] = p_load_nt<false, RAG>(xp + (int64_t)n * Q);
     }
   };
   int64_t t = (int64_t)blockIdx.x * kMidWaves + wave;
@@ -510,7 +592,10 @@ __global__ __launch_bounds__(64 * kMidWaves) __attribute__((amdgpu_waves_per_eu(
     for (int rr = 0; rr < R; rr += 4) {  // four rows of 64 columns per instruction
       const int r = rr + (lane >> 4);
       const int qq = (lane & 15) * 4;
-      if (r < R && q0 + qq < Q) {
+      if (RAG && r < R) {
+        const f4 val = *reinterpret_cast<const f4 *>(stg + r * 64 + qq);
+        p_store_ragged(out + (p * R + r) * Q, q0 + qq, q0 + qq, 4, Q, val, acc_out);
+      } else if (r < R && q0 + qq < Q) {
         f4 *o = reinterpret_cast<f4 *>(out + (p * R + r) * Q + q0 + qq);
         f4 val = *reinterpret_cast<const f4 *>(stg + r * 64 + qq);
         if (acc_out) {
@@ -545,7 +630,7 @@ __global__ __launch_bounds__(64 * kMidWaves) __attribute__((amdgpu_waves_per_eu(
 constexpr int kLdsThreads = 512;
 constexpr int kLdsWaves = kLdsThreads / 64;
 
-template <bool BF, int RT, int CPR, int NB>
+template <bool BF, int RT, int CPR, int NB, bool RAG>
 __global__ __launch_bounds__(kLdsThreads) __attribute__((amdgpu_waves_per_eu(CPR <= 16 ? 4 : 1))) void ttm_last_lds_k(const void *__restrict__ Xv, int64_t M,
                                                               int K, const float *__restrict__ F,
                                                               int64_t ldl, int64_t ldr, int R,
@@ -568,8 +653,9 @@ __global__ __launch_bounds__(kLdsThreads) __attribute__((amdgpu_waves_per_eu(CPR
   const int FR = RP < R + 1 ? RP : R + 1;
   uint16_t *hi = reinterpret_cast<uint16_t *>(lds_b);
   uint16_t *lo = hi + FR * KS;
+  uint16_t *lo2 = lo + FR * KS;  // ragged BF16 only: the third part of the factor
   float *fl = reinterpret_cast<float *>(lds_b);
-  const int fbytes = BF ? 2 * FR * KS * 2 : FR * KS * 4;  // a multiple of 16
+  const int fbytes = BF ? (RAG ? 3 : 2) * FR * KS * 2 : FR * KS * 4;  // a multiple of 16
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
   const int li = lane & 15, lg = lane >> 4;
@@ -587,16 +673,28 @@ __global__ __launch_bounds__(kLdsThreads) __attribute__((amdgpu_waves_per_eu(CPR
   // go to LDS untouched, which keeps the waits exact.
   auto load_piece = [&](u4 (&b)[LPI], int64_t t, int h) {
     const int k = h * KC + cch * EPC;
-    const int kc = k < K ? k : 0;
+    const int kc = k < K ? (RAG ? min(k, K - EPC) : k) : 0;
 #pragma unroll
     for (int j = 0; j < LPI; ++j) {
       int64_t row = t * 16 + j * RPI + crow;
       row = row < M ? row : M - 1;
-      b[j] = __builtin_nontemporal_load(reinterpret_cast<const u4 *>(
-          reinterpret_cast<const char *>(Xv) + (row * ldx + kc) * ESZ));
+      b[j] = p_load_nt<BF, RAG>(reinterpret_cast<const char *>(Xv) + (row * ldx + kc) * ESZ);
     }
   };
-  auto store_piece = [&](const u4 (&b)[LPI]) {
+  // RAG: the row's last, partial chunk was read EPC - K % EPC elements early
+  const int tail_bits = RAG ? (EPC - K % EPC) % EPC * ESZ * 8 : 0;
+  auto store_piece = [&](const u4 (&b0)[LPI], int h) {
+    u4 b[LPI];
+#pragma unroll
+    for (int j = 0; j < LPI; ++j) b[j] = b0[j];
+    if (RAG && tail_bits && h == kpt - 1) {
+      const int k = h * KC + cch * EPC;
+#pragma unroll
+      for (int j = 0; j < LPI; ++j) {
+        const u4 w = p_shift_down(b[j], tail_bits);
+        if (k < K && k + EPC > K) b[j] = w;
+      }
+    }
 #pragma unroll
     for (int j = 0; j < LPI; ++j)
       *reinterpret_cast<u4 *>(stg + (j * RPI + crow) * SS + cch * 16) = b[j];
@@ -618,6 +716,7 @@ __global__ __launch_bounds__(kLdsThreads) __attribute__((amdgpu_waves_per_eu(CPR
           const int off = min(nt * 16 + li, FR - 1) * KS + kk + 8 * lg;
           acc[nt] = p_mfma_bf16(a, *reinterpret_cast<const u4 *>(hi + off), acc[nt]);
           acc[nt] = p_mfma_bf16(a, *reinterpret_cast<const u4 *>(lo + off), acc[nt]);
+          if (RAG) acc[nt] = p_mfma_bf16(a, *reinterpret_cast<const u4 *>(lo2 + off), acc[nt]);
         }
       } else {
         const f4 xv = __builtin_bit_cast(f4, a);
@@ -648,7 +747,11 @@ __global__ __launch_bounds__(kLdsThreads) __attribute__((amdgpu_waves_per_eu(CPR
 #pragma unroll
       for (int e0 = 0; e0 < 16 * RP; e0 += 256) {
         const int e = e0 + 4 * lane;
-        if (e + 4 <= nfl) {
+        if (RAG && e + 4 <= nfl) {  // the output may start at any element
+          f4 val = *reinterpret_cast<const f4 *>(ot + e);
+          if (acc_out) val += *reinterpret_cast<const f4_el *>(dst + e);
+          *reinterpret_cast<f4_el *>(dst + e) = val;
+        } else if (e + 4 <= nfl) {
           f4 val = *reinterpret_cast<const f4 *>(ot + e);
           if (acc_out) {  // a later chunk of the contracted index: added in chunk order
             val += *reinterpret_cast<const f4 *>(dst + e);
@@ -691,7 +794,9 @@ __global__ __launch_bounds__(kLdsThreads) __attribute__((amdgpu_waves_per_eu(CPR
   auto fac_store = [&](int k, float x) {
     const float a = (k < K && fr < R) ? x : 0.f;
     const int kk = k < Kp ? k : Kp;
-    if (BF) {
+    if (BF && RAG) {
+      p_split3(a, hi + frs * KS + kk, lo + frs * KS + kk, lo2 + frs * KS + kk);
+    } else if (BF) {
       const uint16_t h = p_f2bf(a);
       hi[frs * KS + kk] = h;
       lo[frs * KS + kk] = p_f2bf(a - p_bf2f(h));
@@ -722,7 +827,7 @@ __global__ __launch_bounds__(kLdsThreads) __attribute__((amdgpu_waves_per_eu(CPR
   if (gw >= ntile) return;  // no barrier follows
   const int64_t np = ((ntile - 1 - gw) / tstride + 1) * kpt;  // pieces of this wave
   auto step = [&](u4 (&b)[LPI]) {
-    store_piece(b);
+    store_piece(b, ch);
     load_piece(b, lt, lh);
     adv(lt, lh);
     __builtin_amdgcn_sched_barrier(0);
@@ -769,9 +874,9 @@ size_t pass_last_lds(bool bf, int RT, int64_t K) {
 
 // Earlier-mode kernels: the factor (bf16 hi / lo rows, or FP32 rows) plus each wave's
 // output staging.
-size_t pass_mid_lds(bool bf, int RT, int64_t N, int64_t R, bool hs) {
+size_t pass_mid_lds(bool bf, int RT, int64_t N, int64_t R, bool hs, bool rag) {
   const int64_t Np = (N + 31) / 32 * 32;
-  if (bf) return (size_t)(2 * 16 * RT * (Np + 8) * 2 + (int64_t)kMidWaves * R * (hs ? 64 : 128) * 4);
+  if (bf) return (size_t)((rag ? 3 : 2) * 16 * RT * (Np + 8) * 2 + (int64_t)kMidWaves * R * (hs ? 64 : 128) * 4);
   return (size_t)(Np * (16 * RT + 2) * 4 + (int64_t)kMidWaves * R * 64 * 4);
 }
 
@@ -792,29 +897,32 @@ int device_cu_count() {
   return n;
 }
 
-size_t last_lds_bytes(bool bf, int RT, int CPR, int64_t K, int64_t R) {
+size_t last_lds_bytes(bool bf, int RT, int CPR, int64_t K, int64_t R, bool rag) {
   const int64_t EPC = bf ? 8 : 4, KC = CPR * EPC;
   const int64_t Kp = (K + KC - 1) / KC * KC;
   const int64_t KS = Kp + (bf ? 8 : 4);
   const int64_t FR = std::min<int64_t>(16 * RT, R + 1);
-  const int64_t fbytes = bf ? 2 * FR * KS * 2 : FR * KS * 4;
+  const int64_t fbytes = bf ? (rag ? 3 : 2) * FR * KS * 2 : FR * KS * 4;
   return (size_t)(fbytes + (int64_t)kLdsWaves * 16 * (CPR * 16 + 16));
 }
 
 static nnc_status launch_last_lds(const void *X, bool bf, int64_t M, int64_t K, const float *F,
                                   int64_t ldl, int64_t ldr, int64_t R, float *out, hipStream_t s,
-                                  const char **kernel_name, int reserve, int64_t ldx, int acc_out) {
+                                  const char **kernel_name, int reserve, int64_t ldx, int acc_out, bool rag) {
   const int EPC = bf ? 8 : 4;
-  if (K % EPC || K > (1 << 20) || K < 8 * EPC) return NNC_EUNSUPPORTED;
+  // ragged rows shorter than the narrowest piece (8 chunks) leave its other chunks idle; rows
+  // shorter than one chunk stay with the general kernel
+  if (K > (1 << 20) || (rag ? K < EPC : K % EPC || K < 8 * EPC)) return NNC_EUNSUPPORTED;
   const int RT = R <= 16 ? 1 : 2;
   // pieces of 16 chunks and two blocks per CU when two blocks' LDS fits a CU (every variant
   // of 16 chunks stays within 128 VGPRs, four waves per SIMD), else the widest pieces that fit
   int CPR = K >= 32 * EPC ? 32 : (K >= 16 * EPC ? 16 : 8), per_cu = 1;
-  if (K >= 16 * EPC && 2 * last_lds_bytes(bf, RT, 16, K, R) <= kCuLdsBytes) {
+  if (K >= 16 * EPC && 2 * last_lds_bytes(bf, RT, 16, K, R, rag) <= kCuLdsBytes) {
     CPR = 16;
     per_cu = 2;
   }
-  const size_t lds = last_lds_bytes(bf, RT, CPR, K, R);
+  while (rag && CPR > 8 && last_lds_bytes(bf, RT, CPR, K, R, rag) > kCuLdsBytes) CPR >>= 1;
+  const size_t lds = last_lds_bytes(bf, RT, CPR, K, R, rag);
   if (lds > kCuLdsBytes) return NNC_EUNSUPPORTED;
   const int64_t tiles = (M + 15) / 16;
   const int grid = (int)std::max<int64_t>(
@@ -823,12 +931,18 @@ static nnc_status launch_last_lds(const void *X, bool bf, int64_t M, int64_t K, 
   // one piece in flight per wave (measured fastest at 512^3 with random data, 51.5-52 us
   // against 53.5-54 with two and 54-55 with three for bf16 X: with the HBM saturated, more
   // outstanding loads only queue)
-#define NNC_LL(BFV, RTV, CPRV)                                                                    \
-  do {                                                                                            \
-    constexpr int NBV = 1;                                                                        \
-    NNC_TRY(allow_lds_bytes(reinterpret_cast<const void *>(ttm_last_lds_k<BFV, RTV, CPRV, NBV>), lds)); \
-    hipLaunchKernelGGL((ttm_last_lds_k<BFV, RTV, CPRV, NBV>), dim3(grid), dim3(kLdsThreads), lds, s, X, \
-                       M, (int)K, F, ldl, ldr, (int)R, out, ldx, acc_out);                        \
+#define NNC_LLR(BFV, RTV, CPRV, RAGV)                                                                   \
+  do {                                                                                                  \
+    NNC_TRY(allow_lds_bytes(reinterpret_cast<const void *>(ttm_last_lds_k<BFV, RTV, CPRV, 1, RAGV>), lds)); \
+    hipLaunchKernelGGL((ttm_last_lds_k<BFV, RTV, CPRV, 1, RAGV>), dim3(grid), dim3(kLdsThreads), lds, s, X, \
+                       M, (int)K, F, ldl, ldr, (int)R, out, ldx, acc_out);                              \
+  } while (0)
+#define NNC_LL(BFV, RTV, CPRV)          \
+  do {                                  \
+    if (rag)                            \
+      NNC_LLR(BFV, RTV, CPRV, true);    \
+    else                                \
+      NNC_LLR(BFV, RTV, CPRV, false);   \
   } while (0)
 #define NNC_LL_CPR(BFV, RTV)           \
   do {                                 \
@@ -849,7 +963,10 @@ static nnc_status launch_last_lds(const void *X, bool bf, int64_t M, int64_t K, 
     NNC_LL_CPR(false, 2);
 #undef NNC_LL_CPR
 #undef NNC_LL
-  if (kernel_name) *kernel_name = bf ? "ttm_last_lds_bf16" : "ttm_last_lds_f32";
+#undef NNC_LLR
+  if (kernel_name)
+    *kernel_name = rag ? (bf ? "ttm_last_lds_bf16 (ragged)" : "ttm_last_lds_f32 (ragged)")
+                       : (bf ? "ttm_last_lds_bf16" : "ttm_last_lds_f32");
   NNC_HIP(hipGetLastError());
   return NNC_OK;
 }
@@ -862,38 +979,43 @@ nnc_status launch_pass(const void *X, nnc_dtype xdt, int64_t P, int64_t N, int64
                        int64_t ldl, int64_t ldr, int64_t R, float *out, hipStream_t s,
                        const char **kernel_name, int reserve_cus) {
   if (R > 32 || R < 1) return NNC_EUNSUPPORTED;
-  if ((reinterpret_cast<uintptr_t>(X) & 15u) || (reinterpret_cast<uintptr_t>(out) & 15u))
-    return NNC_EUNSUPPORTED;
   const bool bf = xdt == NNC_BF16;
+  // rows (of X and of the output) that do not all start at a 16-byte boundary: the ragged
+  // variants, for pointers at element boundaries
+  const bool rag = ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(out)) & 15u) ||
+                   (Q == 1 ? N : Q) % (bf ? 8 : 4);
+  if ((reinterpret_cast<uintptr_t>(X) & (bf ? 1u : 3u)) || (reinterpret_cast<uintptr_t>(out) & 3u))
+    return NNC_EUNSUPPORTED;
   const int esz = bf ? 2 : 4;
   const int RT = R <= 16 ? 1 : 2;
   const int waves = kPassThreads / 64;
   if (Q == 1) {
     if (N > (1 << 20)) return NNC_EUNSUPPORTED;
-    nnc_status st = launch_last_lds(X, bf, P, N, F, ldl, ldr, R, out, s, kernel_name, reserve_cus, N, 0);
+    nnc_status st = launch_last_lds(X, bf, P, N, F, ldl, ldr, R, out, s, kernel_name, reserve_cus, N, 0, rag);
     if (st != NNC_EUNSUPPORTED) return st;
-    const int EPC = bf ? 8 : 4, KC = 32 * EPC;
-    if (N % EPC == 0 && N >= 8 * EPC && last_lds_bytes(bf, RT, 32, KC, R) <= kCuLdsBytes) {
+    // (ragged rows: a multiple of the narrowest piece, any slab longer than one 16-byte chunk)
+    const int EPC = bf ? 8 : 4, cpr = rag ? 8 : 32, KC = cpr * EPC, last_min = rag ? EPC : 8 * EPC;
+    if ((rag || N % EPC == 0) && N >= 8 * EPC && last_lds_bytes(bf, RT, cpr, KC, R, rag) <= kCuLdsBytes) {
       // chunks of Kc (a multiple of the 32-chunk piece width, so every slab starts 16-byte
       // aligned), the last one long enough for the kernel's pieces
       int64_t Kmax = KC;
-      while (last_lds_bytes(bf, RT, 32, Kmax + KC, R) <= kCuLdsBytes) Kmax += KC;
+      while (last_lds_bytes(bf, RT, cpr, Kmax + KC, R, rag) <= kCuLdsBytes) Kmax += KC;
       int64_t Kc = Kmax, nch = 1;
       for (; Kc >= KC; Kc -= KC) {
         nch = (N + Kc - 1) / Kc;
-        if (N - (nch - 1) * Kc >= 8 * EPC) break;
+        if (N - (nch - 1) * Kc >= last_min) break;
       }
       if (Kc >= KC) {
         for (int64_t c = 0; c < nch; ++c) {
           const int64_t k0 = c * Kc, kc = std::min(Kc, N - k0);
           NNC_TRY(launch_last_lds(static_cast<const char *>(X) + k0 * esz, bf, P, kc, F + k0 * ldl, ldl, ldr, R,
-                                  out, s, nullptr, reserve_cus, N, c > 0));
+                                  out, s, nullptr, reserve_cus, N, c > 0, rag));
         }
         if (kernel_name) *kernel_name = bf ? "ttm_last_lds_bf16 (chunked)" : "ttm_last_lds_f32 (chunked)";
         return NNC_OK;
       }
     }
-    if (N % (bf ? 8 : 4)) return NNC_EUNSUPPORTED;
+    if (rag) return NNC_EUNSUPPORTED;
     const size_t lds = pass_last_lds(bf, RT, N);
     if (lds > kPassLdsMax) return NNC_EUNSUPPORTED;
     const int64_t tiles = (P + 15) / 16;
@@ -912,21 +1034,21 @@ nnc_status launch_pass(const void *X, nnc_dtype xdt, int64_t P, int64_t N, int64
     if (kernel_name) *kernel_name = bf ? "ttm_last_pipe_bf16" : "ttm_last_pipe_f32";
   } else {
     // earlier mode: ttm_mid_lds_k (bf16 X) / ttm_mid_lds_f32_k (FP32 X)
-    if (Q % (bf ? 8 : 4)) return NNC_EUNSUPPORTED;
+    if (Q < (bf ? 8 : 4)) return NNC_EUNSUPPORTED;
     if (N > (1 << 20) || N * ldl + R * ldr >= ((int64_t)1 << 31)) return NNC_EUNSUPPORTED;  // 32-bit factor indexing
     // bf16 output staging by halves of the tile when the whole tile's does not fit beside the
     // factor (R above 20 at N = 512); rows of the factor per launch: all of them, or chunks of
     // a multiple of 32
-    const bool hs = bf && pass_mid_lds(bf, RT, N, R, false) > kCuLdsBytes;
+    const bool hs = bf && pass_mid_lds(bf, RT, N, R, false, rag) > kCuLdsBytes;
     int64_t Nc = N;
-    if (pass_mid_lds(bf, RT, N, R, hs) > kCuLdsBytes) {
+    if (pass_mid_lds(bf, RT, N, R, hs, rag) > kCuLdsBytes) {
       int64_t Nmax = 0;
-      while (pass_mid_lds(bf, RT, Nmax + 32, R, hs) <= kCuLdsBytes) Nmax += 32;
+      while (pass_mid_lds(bf, RT, Nmax + 32, R, hs, rag) <= kCuLdsBytes) Nmax += 32;
       if (Nmax == 0) return NNC_EUNSUPPORTED;
       const int64_t nch = (N + Nmax - 1) / Nmax;
       Nc = ((N + nch - 1) / nch + 31) / 32 * 32;
     }
-    const size_t lds = pass_mid_lds(bf, RT, Nc, R, hs);
+    const size_t lds = pass_mid_lds(bf, RT, Nc, R, hs, rag);
     const int64_t tiles = P * ((Q + (bf ? 127 : 63)) / (bf ? 128 : 64));
     // two blocks per CU when their LDS fits and the variant stays within 128 VGPRs (four
     // waves per SIMD: the FP32 kernels and the bf16 ones of one rank tile)
@@ -946,20 +1068,29 @@ nnc_status launch_pass(const void *X, nnc_dtype xdt, int64_t P, int64_t N, int64
   } while (0)
       if (bf) {
 #define XARG (const uint16_t *)Xc
-        if (RT == 1 && !hs) NNC_MID((ttm_mid_lds_k<1, false>));
-        else if (RT == 1) NNC_MID((ttm_mid_lds_k<1, true>));
-        else if (!hs) NNC_MID((ttm_mid_lds_k<2, false>));
-        else NNC_MID((ttm_mid_lds_k<2, true>));
+        if (rag) {
+          if (RT == 1 && !hs) NNC_MID((ttm_mid_lds_k<1, false, true>));
+          else if (RT == 1) NNC_MID((ttm_mid_lds_k<1, true, true>));
+          else if (!hs) NNC_MID((ttm_mid_lds_k<2, false, true>));
+          else NNC_MID((ttm_mid_lds_k<2, true, true>));
+        } else if (RT == 1 && !hs) NNC_MID((ttm_mid_lds_k<1, false, false>));
+        else if (RT == 1) NNC_MID((ttm_mid_lds_k<1, true, false>));
+        else if (!hs) NNC_MID((ttm_mid_lds_k<2, false, false>));
+        else NNC_MID((ttm_mid_lds_k<2, true, false>));
 #undef XARG
       } else {
 #define XARG (const float *)Xc
-        if (RT == 1) NNC_MID((ttm_mid_lds_f32_k<1, kMidDepthF32>));
-        else NNC_MID((ttm_mid_lds_f32_k<2, kMidDepthF32>));
+        if (rag && RT == 1) NNC_MID((ttm_mid_lds_f32_k<1, kMidDepthF32, true>));
+        else if (rag) NNC_MID((ttm_mid_lds_f32_k<2, kMidDepthF32, true>));
+        else if (RT == 1) NNC_MID((ttm_mid_lds_f32_k<1, kMidDepthF32, false>));
+        else NNC_MID((ttm_mid_lds_f32_k<2, kMidDepthF32, false>));
 #undef XARG
       }
 #undef NNC_MID
     }
-    if (kernel_name)
+    if (kernel_name && rag)
+      *kernel_name = bf ? "ttm_mid_bf16 (ragged)" : "ttm_mid_f32 (ragged)";
+    else if (kernel_name)
       *kernel_name = Nc < N ? (bf ? "ttm_mid_bf16 (chunked)" : "ttm_mid_f32 (chunked)") : (bf ? "ttm_mid_bf16" : "ttm_mid_f32");
   }
   NNC_HIP(hipGetLastError());
