@@ -244,8 +244,7 @@ static nnc_status ttm_mode(const void *in, nnc_dtype dt, int d, const int64_t *c
 // of mode k from a rank index back to a data index.
 static nnc_status expand_mode(const float *in, int d, const int64_t *cur, int k, const float *A,
                               int64_t N, float *out, hipStream_t s) {
-  return launch_ttm(in, NNC_F32, prod(cur, 0, k), cur[k], prod(cur, k + 1, d), A, 1, cur[k], N, out,
-                    s, false);
+  return launch_expand(in, prod(cur, 0, k), cur[k], prod(cur, k + 1, d), A, N, out, s);
 }
 
 // Chain of contractions of the modes in `modes` (in order) of `src` (dims cur, updated in

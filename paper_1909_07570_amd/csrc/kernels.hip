@@ -110,6 +110,153 @@ nnc_status launch_ttm(const void *X, nnc_dtype xdt, int64_t P, int64_t N, int64_
 }
 
 // =====================================================================================
+// Expansion of a rank mode to a data mode: out[p][n][q] = sum_r A[n][r] in[p][r][q], R <= 32
+// (A row-major N x R), summed in rank order.  Bound by the write of out.
+//   expand_wide_k  : long rows q: a thread keeps its column's R inputs (V adjacent columns) and
+//                    walks a range of n, whose factor row is uniform over the block.
+//   expand_short_k : short rows: out[p] is one contiguous block of N Q values; a thread keeps
+//                    the factor row of its (n, q .. q + V - 1) and walks p, whose R x Q inputs
+//                    pass through LDS a few p at a time.
+// Measured (in brackets: the general contraction kernel, one thread per output column walking
+// n): 64^4 x 8 from 64^3 x 8 x 8 125 us (560), 128^3 x 16 36 us (230), 256^2 x 32 12 us (26).
+// The line between the two is where a row of q fills a block.
+// =====================================================================================
+template <int V>
+struct ExpVec {
+  float v[V];
+};
+template <int V>
+static __device__ inline ExpVec<V> exp_load(const float *p) {
+  ExpVec<V> x;
+  if (V == 4) {
+    const f4 y = *reinterpret_cast<const f4 *>(p);
+#pragma unroll
+    for (int i = 0; i < V; ++i) x.v[i] = y[i];
+  } else {
+    x.v[0] = *p;
+  }
+  return x;
+}
+template <int V>
+static __device__ inline void exp_store(float *p, const ExpVec<V> &x) {
+  if (V == 4)
+    *reinterpret_cast<f4 *>(p) = f4{x.v[0], x.v[V > 1 ? 1 : 0], x.v[V > 2 ? 2 : 0], x.v[V > 3 ? 3 : 0]};
+  else
+    *p = x.v[0];
+}
+
+template <int RB, int V>
+__global__ __launch_bounds__(256) void expand_wide_k(const float *__restrict__ in, int64_t P, int64_t R, int64_t Q,
+                                                     const float *__restrict__ A, int64_t N, int64_t nper,
+                                                     float *__restrict__ out) {
+  const int64_t qv = Q / V;
+  const int64_t n0 = blockIdx.y * nper, n1 = n0 + nper < N ? n0 + nper : N;
+  for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < P * qv; idx += (int64_t)gridDim.x * 256) {
+    const int64_t p = idx / qv, q = (idx - p * qv) * V;
+    ExpVec<V> x[RB];
+#pragma unroll
+    for (int r = 0; r < RB; ++r) x[r] = exp_load<V>(in + (p * R + (r < R ? r : 0)) * Q + q);
+    for (int64_t n = n0; n < n1; ++n) {
+      const float *a = A + n * R;
+      ExpVec<V> acc;
+#pragma unroll
+      for (int i = 0; i < V; ++i) acc.v[i] = 0.f;
+#pragma unroll
+      for (int r = 0; r < RB; ++r)
+        if (r < R) {
+          const float f = a[r];
+#pragma unroll
+          for (int i = 0; i < V; ++i) acc.v[i] = fmaf(f, x[r].v[i], acc.v[i]);
+        }
+      exp_store<V>(out + (p * N + n) * Q + q, acc);
+    }
+  }
+}
+
+constexpr int kExpLds = 4096;  // floats of inputs staged at a time (whole p)
+
+template <int RB, int V>
+__global__ __launch_bounds__(256) void expand_short_k(const float *__restrict__ in, int64_t P, int R, int Q,
+                                                      const float *__restrict__ A, int N, int64_t pper, int pb,
+                                                      float *__restrict__ out) {
+  extern __shared__ __attribute__((aligned(16))) float xs[];
+  const int nq = N * Q, rq = R * Q;
+  const int e = (blockIdx.x * 256 + threadIdx.x) * V;
+  const bool act = e < nq;
+  const int n = act ? e / Q : 0, q = act ? e - n * Q : 0;
+  float a[RB];
+#pragma unroll
+  for (int r = 0; r < RB; ++r) a[r] = r < R ? A[(int64_t)n * R + r] : 0.f;
+  const int64_t p0 = blockIdx.y * pper, p1 = p0 + pper < P ? p0 + pper : P;
+  for (int64_t pc = p0; pc < p1; pc += pb) {
+    const int np = (int)(p1 - pc < pb ? p1 - pc : pb);
+    __syncthreads();
+    for (int x = threadIdx.x * V; x < np * rq; x += 256 * V) exp_store<V>(xs + x, exp_load<V>(in + pc * rq + x));
+    __syncthreads();
+    if (!act) continue;
+    for (int j = 0; j < np; ++j) {
+      ExpVec<V> acc;
+#pragma unroll
+      for (int i = 0; i < V; ++i) acc.v[i] = 0.f;
+      const float *xp = xs + j * rq + q;
+#pragma unroll
+      for (int r = 0; r < RB; ++r)
+        if (r < R) {
+          const ExpVec<V> x = exp_load<V>(xp + r * Q);
+#pragma unroll
+          for (int i = 0; i < V; ++i) acc.v[i] = fmaf(a[r], x.v[i], acc.v[i]);
+        }
+      exp_store<V>(out + (pc + j) * nq + e, acc);
+    }
+  }
+}
+
+nnc_status launch_expand(const float *in, int64_t P, int64_t R, int64_t Q, const float *A, int64_t N, float *out,
+                         hipStream_t s) {
+  const bool v4 = Q % 4 == 0 && aligned16(in) && aligned16(out);
+  const int64_t nq = N * Q;
+  if (R > 32 || nq >= (1 << 24)) return launch_ttm(in, NNC_F32, P, R, Q, A, 1, R, N, out, s, false);
+  if (Q >= 256 || R * Q > 2 * kExpLds) {
+    const int64_t cols = P * (v4 ? Q / 4 : Q), bx = std::min<int64_t>((cols + 255) / 256, 65535);
+    // ranges of n: enough blocks for the chip, at least 4 rows each
+    const int64_t by = std::min<int64_t>(std::max<int64_t>(1, 2048 / bx), (N + 3) / 4), nper = (N + by - 1) / by;
+#define NNC_EXP(RBV, VV)                                                                                     \
+  hipLaunchKernelGGL((expand_wide_k<RBV, VV>), dim3((unsigned)bx, (unsigned)((N + nper - 1) / nper)), dim3(256), 0, \
+                     s, in, P, R, Q, A, N, nper, out)
+#define NNC_EXP_R(VV)          \
+  do {                         \
+    if (R <= 8)                \
+      NNC_EXP(8, VV);          \
+    else if (R <= 16)          \
+      NNC_EXP(16, VV);         \
+    else                       \
+      NNC_EXP(32, VV);         \
+  } while (0)
+    if (v4)
+      NNC_EXP_R(4);
+    else
+      NNC_EXP_R(1);
+#undef NNC_EXP
+  } else {
+    const int64_t bx = (nq / (v4 ? 4 : 1) + 255) / 256;
+    const int64_t by = std::min<int64_t>(std::max<int64_t>(1, 2048 / bx), P), pper = (P + by - 1) / by;
+    const int pb = (int)std::min<int64_t>(std::max<int64_t>(1, kExpLds / (R * Q)), pper);
+    const size_t lds = sizeof(float) * (size_t)(pb * R * Q);
+#define NNC_EXP(RBV, VV)                                                                                      \
+  hipLaunchKernelGGL((expand_short_k<RBV, VV>), dim3((unsigned)bx, (unsigned)((P + pper - 1) / pper)), dim3(256), lds, \
+                     s, in, P, (int)R, (int)Q, A, (int)N, pper, pb, out)
+    if (v4)
+      NNC_EXP_R(4);
+    else
+      NNC_EXP_R(1);
+#undef NNC_EXP
+#undef NNC_EXP_R
+  }
+  NNC_HIP(hipGetLastError());
+  return NNC_OK;
+}
+
+// =====================================================================================
 // Small dense steps of the multiplicative updates.
 // =====================================================================================
 __global__ void contract_except_k(const float *__restrict__ U, const float *__restrict__ V,
@@ -459,81 +606,179 @@ constexpr int kResidMaxBlocks = 2048;
 int resid_stream_max_blocks() { return kResidMaxBlocks; }
 
 // ||X - Xhat||^2 and ||X||^2 with Xhat[m][k] = sum_r W[m][r] Ad[k][r] (X viewed as M x K,
-// W the expansion of every mode but the last, Ad the last factor).  A block takes tiles of
-// kResidRows rows: the tile's W rows go to LDS, each thread keeps the factor rows of its
-// columns k = t + 256 j (j < kResidCols) in registers and reads X along rows (coalesced).
-// Each difference is formed and squared in FP64; sums are FP64 per thread, then per block.
-// Rows past M are read clamped and left out of the sums by a predicate (not a loop exit), so
-// the products of the tile's rows can interleave.
-constexpr int kResidRows = 16;
+// W the expansion of every mode but the last, Ad the last factor), R <= 32.
+// A wave owns a stripe of 64 NS columns (NS adjacent columns a lane, their factor rows in
+// registers for the whole stripe) and walks X's rows, 8 or 16 at a time with the next ones'
+// loads in flight: X is read once in whole row segments, straight into the layout of its products.  Those run on the FP32 matrix cores
+// as 4 x 4 x 1 blocks, one per four lanes: a block's four columns are its lanes', its four rows
+// are X's, and W's 4 x 16 entries (four rows, sixteen ranks) sit in one register whose block r
+// the instruction broadcasts to all (cbsz 4, abid r), so a row group costs R / 16 loads of W.
+// Products add rank by rank in FP32, as a chain of fused multiply-adds would.  Each difference
+// is formed and squared in FP64; sums are FP64 per lane, then per block.
+// Bound: the read of X; the matrix cores need 8 R cycles per 64 NS x 4 entries, the FP64 side
+// about 20 per 64.  Rows past M are read clamped and left out of the sums.
+// Measured (in brackets: one thread per column with all ranks as VALU products, which left
+// threads idle where K < 256): 64^5 FP32 at R = 8 892 us (2996), 128^4 BF16 at R = 16 176 us
+// (488), 512^3 FP32 at R = 20 123 us (152), 256^3 FP32 at R = 32 29 us (59).
+constexpr int kResidWaves = kResidThreads / 64;
 
-template <typename XT, int RB, int kResidCols>  // columns per thread per chunk (1 when K <= 256)
-__global__ __launch_bounds__(kResidThreads) void resid_stream_k(const XT *__restrict__ X, int64_t M,
-                                                                int64_t K, const float *__restrict__ W,
-                                                                const float *__restrict__ Ad,
-                                                                int R, double *__restrict__ part) {
-  __shared__ __attribute__((aligned(16))) float Ws[kResidRows][RB];
+// NS adjacent elements of X at any element boundary, as loaded, and as floats.
+template <typename XT, int NS>
+struct ResidRaw;
+template <>
+struct ResidRaw<float, 1> {
+  static constexpr int kRows = 16;  // rows a wave loads at a time (one such tile is in flight
+  float x;                          // while the one before is used)
+  __device__ void load(const float *p) { x = *p; }
+  __device__ float get(int) const { return x; }
+};
+template <>
+struct ResidRaw<float, 2> {
+  typedef float f2_el __attribute__((ext_vector_type(2), aligned(4)));
+  static constexpr int kRows = 8;
+  float x, y;
+  __device__ void load(const float *p) {
+    const f2_el v = *reinterpret_cast<const f2_el *>(p);
+    x = v[0];
+    y = v[1];
+  }
+  __device__ float get(int s) const { return s ? y : x; }
+};
+template <>
+struct ResidRaw<uint16_t, 1> {
+  static constexpr int kRows = 16;
+  uint16_t x;
+  __device__ void load(const uint16_t *p) { x = *p; }
+  __device__ float get(int) const { return bf2f(x); }
+};
+template <>
+struct ResidRaw<uint16_t, 2> {
+  typedef uint32_t u1_el __attribute__((aligned(2)));
+  static constexpr int kRows = 16;
+  uint32_t x;
+  __device__ void load(const uint16_t *p) { x = *reinterpret_cast<const u1_el *>(p); }
+  __device__ float get(int s) const { return __uint_as_float(s ? x & 0xffff0000u : x << 16); }
+};
+
+template <int RB, int r>
+struct ResidChain {
+  template <int NS>
+  static __device__ inline void run(const float (&w)[(RB + 15) / 16], const float (&b)[NS][RB], f4 (&acc)[NS]) {
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+      acc[s] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[r / 16], b[s][r], acc[s], 4, r % 16, 0);
+    if constexpr (r + 1 < RB) ResidChain<RB, r + 1>::template run<NS>(w, b, acc);
+  }
+};
+
+// nst stripes; the grid's waves take stripe gw % nst and row tiles gw / nst, + rstep, ...
+// of kRows rows, or, with more stripes than waves, stripes gw, gw + sstep, ... and every row.
+template <typename XT, int RB, int NS>
+__global__ __launch_bounds__(kResidThreads) __attribute__((amdgpu_waves_per_eu(RB * NS > 32 ? 3 : 4))) void resid_stream_k(
+    const XT *__restrict__ X, int64_t M, int64_t K, const float *__restrict__ W, const float *__restrict__ Ad, int R,
+    double *__restrict__ part, int64_t nst, int64_t sstep, int64_t rstep) {
   __shared__ double s0[kResidThreads], s1[kResidThreads];
-  const int t = threadIdx.x;
+  constexpr int RH = (RB + 15) / 16;
+  constexpr int kRows = ResidRaw<XT, NS>::kRows;
+  const int t = threadIdx.x, lane = t & 63;
+  const int64_t gw = (int64_t)blockIdx.x * kResidWaves + __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wrow = lane & 3, wr = lane >> 2;
   double sr = 0.0, sx = 0.0;
-  const int64_t ntile = (M + kResidRows - 1) / kResidRows;
-  constexpr int64_t kChunk = (int64_t)kResidThreads * kResidCols;
-  for (int64_t k0 = 0; k0 < K; k0 += kChunk) {
-    float a[kResidCols][RB];
-    int64_t kc[kResidCols];
-    bool kv[kResidCols];
+  const int64_t ntile = (M + kRows - 1) / kRows;
+  const int64_t row0 = nst <= sstep ? gw / nst : 0;
+  const int64_t st0 = nst <= sstep ? (row0 < rstep ? gw % nst : nst) : gw;
+  for (int64_t st = st0; st < nst; st += sstep) {
+    const int k = ((int)st * 64 + lane) * NS;
+    // a lane whose columns reach past the row reads the row's last NS and drops what is not its own
+    const unsigned kb = (unsigned)(k + NS <= (int)K ? k : (int)K - NS);
+    const bool odd = NS == 2 && k == K - 1;
+    float b[NS][RB];
 #pragma unroll
-    for (int j = 0; j < kResidCols; ++j) {
-      const int64_t k = k0 + t + (int64_t)j * kResidThreads;
-      kv[j] = k < K;
-      kc[j] = kv[j] ? k : K - 1;
+    for (int s = 0; s < NS; ++s) {
+      const int64_t kc = k + s < K ? k + s : (int64_t)K - 1;
+      typedef float f4_el __attribute__((ext_vector_type(4), aligned(4)));
 #pragma unroll
-      for (int r = 0; r < RB; ++r) a[j][r] = (kv[j] && r < R) ? Ad[kc[j] * R + r] : 0.f;
+      for (int r = 0; r < RB; r += 4) {  // four ranks a load: a load of 64 rows costs 64 requests
+        if (r + 4 <= R) {
+          const f4_el v = *reinterpret_cast<const f4_el *>(Ad + kc * R + r);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) b[s][r + i] = v[i];
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) b[s][r + i] = r + i < R ? Ad[kc * R + r + i] : 0.f;
+        }
+      }
     }
-    for (int64_t tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
-      const int64_t m0 = tile * kResidRows;
-      __syncthreads();  // the previous tile's W rows are no longer read
-      for (int e = t; e < kResidRows * RB; e += kResidThreads) {
-        const int row = e / RB, r = e - (e / RB) * RB;
-        const int64_t m = m0 + row;
-        Ws[row][r] = (m < M && r < R) ? W[m * R + r] : 0.f;
+    double lr[NS], lx[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) lr[s] = lx[s] = 0.0;
+    auto load = [&](int64_t tile, ResidRaw<XT, NS> (&xv)[kRows], float (&w)[kRows / 4][RH]) {
+      const int64_t m0 = tile * kRows;
+      const int left = (int)(M - m0 < kRows ? M - m0 : kRows) - 1;  // the tile's last row
+      const XT *x0 = X + m0 * K;
+      const float *wt = W + m0 * R;
+#pragma unroll
+      for (int row = 0; row < kRows; ++row) xv[row].load(x0 + (int64_t)(row < left ? row : left) * K + kb);
+#pragma unroll
+      for (int g = 0; g < kRows / 4; ++g) {
+        const int m = 4 * g + wrow < left ? 4 * g + wrow : left;
+#pragma unroll
+        for (int h = 0; h < RH; ++h) w[g][h] = wt[m * R + (wr + 16 * h < R ? wr + 16 * h : 0)];
       }
-      // the tile's X values, all loads in flight together
-      float xv[kResidRows][kResidCols];
+    };
+    auto use = [&](int64_t tile, const ResidRaw<XT, NS> (&xv)[kRows], const float (&w)[kRows / 4][RH]) {
+      auto rows = [&](int n) {  // the tile's first n rows
 #pragma unroll
-      for (int row = 0; row < kResidRows; ++row) {
-        const int64_t m = (m0 + row) < M ? (m0 + row) : M - 1;
+        for (int g = 0; g < kRows / 4; ++g) {
+          f4 acc[NS];
 #pragma unroll
-        for (int j = 0; j < kResidCols; ++j) xv[row][j] = load_x(X + m * K + kc[j]);
-      }
-      __syncthreads();
+          for (int s = 0; s < NS; ++s) acc[s] = f4{0.f, 0.f, 0.f, 0.f};
+          float wg[RH];
 #pragma unroll
-      for (int row = 0; row < kResidRows; ++row) {
-        const bool rv = m0 + row < M;
-        const float4 *w4 = reinterpret_cast<const float4 *>(&Ws[row][0]);
-        float xh[kResidCols];
+          for (int h = 0; h < RH; ++h) wg[h] = wr + 16 * h < R ? w[g][h] : 0.f;
+          ResidChain<RB, 0>::template run<NS>(wg, b, acc);
 #pragma unroll
-        for (int j = 0; j < kResidCols; ++j) xh[j] = 0.f;
+          for (int i = 0; i < 4; ++i) {
+            if (4 * g + i >= n) continue;
 #pragma unroll
-        for (int r4 = 0; r4 < RB / 4; ++r4) {
-          const float4 w = w4[r4];
-#pragma unroll
-          for (int j = 0; j < kResidCols; ++j) {
-            xh[j] = fmaf(w.x, a[j][4 * r4 + 0], xh[j]);
-            xh[j] = fmaf(w.y, a[j][4 * r4 + 1], xh[j]);
-            xh[j] = fmaf(w.z, a[j][4 * r4 + 2], xh[j]);
-            xh[j] = fmaf(w.w, a[j][4 * r4 + 3], xh[j]);
+            for (int s = 0; s < NS; ++s) {
+              const float xf = odd ? xv[4 * g + i].get(NS - 1) : xv[4 * g + i].get(s);
+              const double x = (double)xf, df = x - (double)acc[s][i];
+              lr[s] += df * df;
+              lx[s] += x * x;
+            }
           }
         }
-#pragma unroll
-        for (int j = 0; j < kResidCols; ++j) {
-          if (!kv[j] || !rv) continue;
-          const double df = (double)xv[row][j] - (double)xh[j];
-          sr += df * df;
-          sx += (double)xv[row][j] * (double)xv[row][j];
-        }
-      }
+      };
+      const int64_t n = M - tile * kRows;
+      if (n >= kRows)
+        rows(kRows);
+      else
+        rows((int)n);
+    };
+    // one tile's loads in flight while the one before is used; the loads past the last tile
+    // read it again
+    ResidRaw<XT, NS> x0[kRows], x1[kRows];
+    float w0[kRows / 4][RH], w1[kRows / 4][RH];
+    auto at = [&](int64_t tile) { return tile < ntile ? tile : ntile - 1; };
+    load(at(row0), x0, w0);
+    for (int64_t tile = row0; tile < ntile; tile += 2 * rstep) {
+      load(at(tile + rstep), x1, w1);
+      __builtin_amdgcn_sched_barrier(0);
+      use(tile, x0, w0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (tile + rstep >= ntile) break;
+      load(at(tile + 2 * rstep), x0, w0);
+      __builtin_amdgcn_sched_barrier(0);
+      use(tile + rstep, x1, w1);
+      __builtin_amdgcn_sched_barrier(0);
     }
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+      if (k + s < K) {
+        sr += lr[s];
+        sx += lx[s];
+      }
   }
   s0[t] = sr;
   s1[t] = sx;
@@ -592,7 +837,7 @@ nnc_status launch_resid_stream(const void *X, nnc_dtype xdt, int64_t M, int64_t 
                                const float *Ad, int64_t R, double *part, int *nblocks_out,
                                hipStream_t s) {
   if (R < 1) return fail(NNC_EINVAL, "residual: rank %lld", (long long)R);
-  if (R > 32) {
+  if (R > 32 || K >= (1 << 30)) {
     const int grid = grid_for(M * K, kResidThreads, kResidMaxBlocks);
     if (xdt == NNC_F32)
       hipLaunchKernelGGL(resid_any_k<float>, dim3(grid), dim3(kResidThreads), 0, s,
@@ -604,23 +849,38 @@ nnc_status launch_resid_stream(const void *X, nnc_dtype xdt, int64_t M, int64_t 
     NNC_HIP(hipGetLastError());
     return NNC_OK;
   }
-  const int64_t ntile = (M + kResidRows - 1) / kResidRows;
-  const int grid = (int)std::min<int64_t>(std::max<int64_t>(ntile, 1), kResidMaxBlocks);
-#define NNC_RES(XT, RBV)                                                                              \
-  do {                                                                                                \
-    if (K <= kResidThreads)                                                                           \
-      hipLaunchKernelGGL((resid_stream_k<XT, RBV, 1>), dim3(grid), dim3(kResidThreads), 0, s,         \
-                         (const XT *)X, M, K, W, Ad, (int)R, part);                                   \
-    else                                                                                              \
-      hipLaunchKernelGGL((resid_stream_k<XT, RBV, 2>), dim3(grid), dim3(kResidThreads), 0, s,         \
-                         (const XT *)X, M, K, W, Ad, (int)R, part);                                   \
+  // NS = 2 columns a lane (wider loads, W's loads shared) unless that leaves half a stripe idle
+  const int64_t half = (K + 63) / 64;
+  const int NS = K >= 2 && (half % 2 == 0 || half > 8) ? 2 : 1;
+  const int rows = xdt == NNC_F32 && NS == 2 ? 8 : 16;  // the kernel's kRows
+  const int64_t ntile = (M + rows - 1) / rows, nst = NS == 2 ? (half + 1) / 2 : half;
+  // as many waves as reside together (four per SIMD on 256 CUs, three with more than 32 factor
+  // values a lane): one round of equal shares
+  const int64_t most = (R + 3) / 4 * 4 * NS > 32 ? 768 : 1024;
+  const int grid = (int)std::min<int64_t>((ntile * nst + kResidWaves - 1) / kResidWaves, most);
+  const int64_t waves = (int64_t)grid * kResidWaves;
+  const int64_t rstep = nst <= waves ? waves / nst : 1, sstep = waves;
+#define NNC_RES(XT, RBV)                                                                                      \
+  do {                                                                                                        \
+    if (NS == 1)                                                                                              \
+      hipLaunchKernelGGL((resid_stream_k<XT, RBV, 1>), dim3(grid), dim3(kResidThreads), 0, s, (const XT *)X,  \
+                         M, K, W, Ad, (int)R, part, nst, sstep, rstep);                                       \
+    else                                                                                                      \
+      hipLaunchKernelGGL((resid_stream_k<XT, RBV, 2>), dim3(grid), dim3(kResidThreads), 0, s, (const XT *)X,  \
+                         M, K, W, Ad, (int)R, part, nst, sstep, rstep);                                       \
   } while (0)
 #define NNC_RES2(XT)                    \
   do {                                  \
-    if (R <= 8) NNC_RES(XT, 8);         \
-    else if (R <= 16) NNC_RES(XT, 16);  \
-    else if (R <= 24) NNC_RES(XT, 24);  \
-    else NNC_RES(XT, 32);               \
+    switch ((R + 3) / 4) {              \
+      case 1: NNC_RES(XT, 4); break;    \
+      case 2: NNC_RES(XT, 8); break;    \
+      case 3: NNC_RES(XT, 12); break;   \
+      case 4: NNC_RES(XT, 16); break;   \
+      case 5: NNC_RES(XT, 20); break;   \
+      case 6: NNC_RES(XT, 24); break;   \
+      case 7: NNC_RES(XT, 28); break;   \
+      default: NNC_RES(XT, 32);         \
+    }                                   \
   } while (0)
   if (xdt == NNC_F32)
     NNC_RES2(float);

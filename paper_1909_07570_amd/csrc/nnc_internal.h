@@ -87,6 +87,10 @@ nnc_status launch_ttm(const void *X, nnc_dtype xdt, int64_t P, int64_t N, int64_
                       int64_t ldl, int64_t ldr, int64_t R, float *out, hipStream_t s,
                       bool allow_mfma, const char **kernel_name = nullptr, int reserve_cus = 0);
 
+// out[p][n][q] = sum_r A[n*R + r] in[p][r][q], n < N: a rank mode back to a data mode.
+nnc_status launch_expand(const float *in, int64_t P, int64_t R, int64_t Q, const float *A, int64_t N, float *out,
+                         hipStream_t s);
+
 // Software-pipelined X-streaming contractions (pass_kernels.hip).  Returns NNC_EUNSUPPORTED
 // without recording an error when the shape does not suit them.
 nnc_status launch_pass(const void *X, nnc_dtype xdt, int64_t P, int64_t N, int64_t Q, const float *F,
