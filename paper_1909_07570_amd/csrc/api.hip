@@ -2115,7 +2115,9 @@ static nnc_status tune_batched(const float *core, const CpProblem &pb, int nbatc
     NNC_HIP(hipMemcpy(base + w.oTunePtr, ptrs.data(), sizeof(float *) * ptrs.size(), hipMemcpyHostToDevice));
     NNC_HIP(hipMemcpy(base + w.oTuneRank, rk.data(), sizeof(int) * nbatch, hipMemcpyHostToDevice));
     for (int tg = 0; tg <= 1 && st == NNC_OK; ++tg) {
-      // reading the tensor from global memory is a distinct layout only when it fits in LDS
+      // reading the tensor from global memory is a distinct layout only when it fits in LDS,
+      // and in nncp_k alone
+      if (tg && nncp_mm_fits(pb, maxr, 256) && nncp_mm_fits(pb, maxr, 512)) continue;
       if (tg && nncp_lds_bytes(pb, maxr, 256, false, true) == nncp_lds_bytes(pb, maxr, 256, false, false)) continue;
       for (int t : {256, 512, 1024}) {
         if (nncp_lds_bytes(pb, maxr, t, false, tg != 0) > 150 * 1024) continue;

@@ -1,5 +1,6 @@
 // Nonnegative CP of a small tensor (the Tucker core) by multiplicative updates, entirely
-// inside one workgroup: the CP factors, their Grams and the update temporaries live in LDS,
+// inside one workgroup (shapes that do not suit cpm_kernels.hip, and the least-squares fit): the
+// CP factors, their Grams and the update temporaries live in LDS,
 // and so does the tensor when it fits.  One workgroup per fit, so a launch can run many
 // independent fits (random restarts, uneven ranks) at once, and every sweep of every fit
 // happens inside that single launch.
@@ -523,6 +524,9 @@ nnc_status launch_nncp(const float *T, const CpProblem &pb, int nbatch, const in
                        float *zscratch, int threads, hipStream_t s, bool als, bool t_global) {
   NNC_TRY(nncp_check_shape(pb, max_rank, threads, als));
   if (threads <= 0) threads = nncp_default_threads(pb, max_rank);
+  if (!als && nncp_mm_fits(pb, max_rank, threads))
+    return launch_nncp_mm(T, pb, nbatch, d_ranks, max_rank, d_factor_ptrs, single_ptrs, iters, eps, d_resid, clips,
+                          threads, s);
   const CpLayout L = cp_layout(pb, max_rank, threads, als, t_global);
   if (L.lds_bytes > kCpLdsBudget)
     return fail(NNC_EUNSUPPORTED, "nnCP working set %lld bytes exceeds the LDS budget", (long long)L.lds_bytes);
@@ -531,8 +535,8 @@ nnc_status launch_nncp(const float *T, const CpProblem &pb, int nbatch, const in
   for (int k = 0; k < kMaxDim; ++k) p0.p[k] = (single_ptrs && k < pb.d) ? single_ptrs[k] : nullptr;
   const size_t lds = (size_t)L.lds_bytes;
   // Orders 2 to 5 have kernels of their own: with the order a constant, the loops over modes
-  // unroll and their index bookkeeping folds away (300 sweeps of a 20^3 core at rank 10:
-  // 4.3 -> 3.3 ms).
+  // unroll and their index bookkeeping folds away (300 multiplicative sweeps of a 20^3 core at
+  // rank 10 here: 4.3 -> 3.3 ms).
 #define NNC_CP_LAUNCH3(RM, ALSV, DCV)                                                                  \
   do {                                                                                                 \
     NNC_TRY(allow_lds(reinterpret_cast<const void *>(nncp_k<RM, ALSV, DCV>), L.lds_bytes));            \

@@ -210,6 +210,12 @@ nnc_status launch_nncp(const float *T, const CpProblem &pb, int nbatch, const in
                        bool t_global = false);
 // Host-side check of a shape for launch_nncp (index ranges, rank, LDS); records the error.
 nnc_status nncp_check_shape(const CpProblem &pb, int max_rank, int threads, bool als = false);
+// The matrix-core form of the multiplicative fit (cpm_kernels.hip), for shapes nncp_mm_fits takes;
+// launch_nncp chooses it (t_global then changes nothing).
+bool nncp_mm_fits(const CpProblem &pb, int max_rank, int threads);
+nnc_status launch_nncp_mm(const float *T, const CpProblem &pb, int nbatch, const int *d_ranks, int max_rank,
+                          float *const *d_factor_ptrs, float *const *single_ptrs, int iters, double eps,
+                          double *d_resid, unsigned long long *clips, int threads, hipStream_t s);
 int64_t nncp_lds_bytes(const CpProblem &pb, int max_rank, int threads, bool als = false,
                        bool t_global = false);
 int64_t nncp_zscratch_floats(const CpProblem &pb, int max_rank);
