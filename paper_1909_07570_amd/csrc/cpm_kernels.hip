@@ -24,8 +24,7 @@
 // Sums run in a fixed order: results are reproducible and do not depend on what else is launched.
 //
 // Measured, us a sweep (nncp_k in brackets): 8^5 at rank 16 12.4 (158), 24^3 at rank 16 7.7, 20^3
-// at rank 10 5.7 (8.5), 10 x 10 x 11 x 10 at rank 8 6.4, 12^3 at rank 6 3.9, 3 x 4 x 5 at rank 5
-// 3.1 (4.6).  The two products of 8^5 take 6.0 and 5.2 thousand of its 30 thousand cycles (4.1
+// at rank 10 5.7 (8.5), 10 x 10 x 11 x 10 at rank 8 6.4 and 12^3 at rank 6 3.9.  The two products of 8^5 take 6.0 and 5.2 thousand of its 30 thousand cycles (4.1
 // each is what the matrix cores need); the rest is twelve phases of 0.7 to 2.3 thousand, chains of
 // a few LDS round trips and, in the updates, an FP64 division.  Sixteen waves were slower: every
 // instruction of a phase then issues four times per SIMD.
@@ -649,10 +648,13 @@ static CpmArgs cpm_args(const CpProblem &pb, int threads) {
   return a;
 }
 
+// Cores of fewer than 512 entries stay with nncp_k: there is little to gain there (4.6 us a sweep
+// of 3 x 4 x 5 at rank 5 against 3.1 here), and such small fits carry every change of rounding far
+// (an order of sums of its own moved single factors 2e-6, as far as either lies from 64 bits).
 // Orders 3 to 5 with modes of at most 64 (one wave forms a Gram, one pass of the block an
 // update) whose working set fits one CU; other shapes stay with nncp_k.
 bool nncp_mm_fits(const CpProblem &pb, int max_rank, int threads) {
-  if (pb.d < 3 || pb.d > 5 || pb.size > (1 << 17) || max_rank > 32) return false;
+  if (pb.d < 3 || pb.d > 5 || pb.size < 512 || pb.size > (1 << 17) || max_rank > 32) return false;
   for (int k = 0; k < pb.d; ++k)
     if (pb.dims[k] > 64) return false;
   threads = std::min(threads, 64 * kCpmWaves);

@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
 # one row and one column; just under and over tiles of 16 and steps of 4; ranks over 16; every
 # order with its groups; fragments in registers (16, 32 a lane) and streamed; modes at the limit
 # of 64 and over it (the general kernel)
-CASES = [((1, 1), 1), ((2, 3), 2), ((17, 5), 7), ((64, 64), 32), ((65, 9), 4), ((3, 4, 5), 5), ((16, 4, 4), 16),
+CASES = [((1, 1), 1), ((8, 8, 8), 7), ((11, 47, 1), 3), ((4, 2, 64), 20), ((2, 3), 2), ((17, 5), 7), ((64, 64), 32), ((65, 9), 4), ((3, 4, 5), 5), ((16, 4, 4), 16),
          ((17, 15, 5), 17), ((20, 20, 20), 10), ((24, 24, 24), 16), ((33, 2, 31), 32), ((5, 4, 3, 2), 3),
          ((16, 16, 16, 16), 8), ((9, 7, 11, 5), 16), ((8, 8, 8, 8, 8), 16), ((7, 2, 3, 5, 4), 9),
          ((3, 4, 2, 5, 3, 4), 6), ((2, 2, 2, 2, 2, 2, 2), 3)]
