@@ -91,3 +91,24 @@ def test_zero_restarts_and_without_truth():
     inits = synth.init_restarts(60, 1, X.shape, (3, 3, 3), 4, 2)
     res = nnc.nncandelinc_restarts(dev(X), 1, (3, 3, 3), 4, dev(inits), 10, 10)
     assert res.congruences is None and np.all(np.isfinite(host(res.rel_errors)))
+
+
+@pytest.mark.parametrize("alg", [1, 2])
+@pytest.mark.parametrize("dims,m,r", [((4, 4, 4), (4, 4, 4), 5), ((4, 3, 2), (5, 1, 4), 3), ((8, 5, 4), (4, 2, 3), 4),
+                                      ((7, 4, 3), (2, 4, 4), 6), ((5, 6, 8), (8, 5, 6), 2), ((8, 8, 8), (8, 8, 8), 8),
+                                      ((1, 1, 1), (1, 1, 1), 1)])
+def test_restarts_size_bounds(alg, dims, m, r):
+    """Sizes on each side of the kernel's bounds of 4 and 8, a few sweeps, at the tolerance above."""
+    nnc = need_gpu()
+    rng = np.random.default_rng(dims[0] * 100 + m[0] * 10 + r)
+    X = rng.random(dims).astype(np.float32).astype(np.float64)
+    inits = synth.init_restarts(60 + alg, alg, dims, m, r, 3)
+    print("case", alg, dims, m, r, flush=True)
+    res = nnc.nncandelinc_restarts(dev(X), alg, m, r, dev(inits), 20, 20, lifted=True)
+    rel, lifted = host(res.rel_errors), host(res.lifted)
+    for j in range(3):
+        parts = synth.unpack_restart(inits[j].astype(np.float64), alg, dims, m, r)
+        r_o, _, C_o = oracle.restart_fit(X, alg, parts, 20, 20, truth=[np.ones((n, r)) for n in dims])
+        assert abs(rel[j] - r_o) <= 1e-4, (j, rel[j], r_o)
+        for c, co in zip(np.split(lifted[j], np.cumsum(dims)[:-1]), C_o):
+            assert np.linalg.norm(c - co) <= 1e-4 * max(1.0, np.linalg.norm(co))
