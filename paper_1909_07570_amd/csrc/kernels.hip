@@ -274,83 +274,70 @@ __global__ void contract_except_k(const float *__restrict__ U, const float *__re
   out[idx] = acc;
 }
 
-// The same contraction for J <= JM (<= 32): one wave per output row i, its lanes striding
-// over the flattened summation index t = p * post + q (lane l takes t = l, l + 64, ...) with
-// JM partial sums each, then a butterfly over the wave.  V (pre x J x post) passes through
-// LDS in chunks of the summation index that every wave of the block shares; U's loads are
-// issued four steps ahead of their products.  Every sum runs in a fixed order.
-constexpr int kCeVlds = 16384;  // floats of V staged in LDS per chunk (64 KB)
+// The same contraction for J <= 32 on the FP32 matrix cores: a block takes 16 output rows, its
+// eight waves one contiguous range each of the flattened summation index t = p * post + q, four
+// values of t a step; the waves' sums are added in order through LDS.  Every value is read straight
+// into the layout of the products, eight steps' loads together, so a block costs about two memory
+// round trips (512 rows, t < 400, J = 20: 8.1 us; a wave per row with V in LDS and a butterfly per
+// column: 17.5 us).  Sums of at most total / 8 products run in order, the rest as a tree's.
+constexpr int kCeWaves = 8;
 
-template <int JM>
-__global__ __launch_bounds__(256) void contract_except_rows_k(const float *__restrict__ U,
-                                                              const float *__restrict__ V, int pre,
-                                                              int64_t I, int J, int post,
-                                                              float *__restrict__ out) {
-  __shared__ float Vs[kCeVlds];
-  const int lane = threadIdx.x & 63;
-  const int64_t i = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  const bool active = i < I;  // every wave takes part in the staging barriers
-  const int total = pre * post;
-  const int tc = (kCeVlds / J) & ~63;  // chunk of the summation index, a multiple of 64
-  float acc[JM];
+template <int RT>
+__global__ __launch_bounds__(64 * kCeWaves) void contract_except_rows_k(const float *__restrict__ U,
+                                                                        const float *__restrict__ V, int pre,
+                                                                        int64_t I, int J, int post,
+                                                                        float *__restrict__ out) {
+  __shared__ f4 part[kCeWaves][RT][64];
+  const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t i0 = (int64_t)blockIdx.x * 16;
+  const int64_t ir = i0 + li < I ? i0 + li : I - 1;  // rows past I are computed and not stored
+  const int total = pre * post, steps = (total + 3) >> 2, per = (steps + kCeWaves - 1) / kCeWaves;
+  const int s1 = min(steps, (wave + 1) * per);
+  const float inv_post = 1.0f / (float)post;
+  int jc[RT];
 #pragma unroll
-  for (int j = 0; j < JM; ++j) acc[j] = 0.f;
-  const int dp = 64 / post, dq = 64 - (64 / post) * post;
-  for (int t0 = 0; t0 < total; t0 += tc) {
-    const int tn = min(tc, total - t0);
-    __syncthreads();  // the previous chunk has been consumed
-    // thread per summation index tt: its J entries of V (stride post) loaded together
-    for (int tt = threadIdx.x; tt < tn; tt += blockDim.x) {
-      const int t = t0 + tt;
-      const int p = t / post, q = t - (t / post) * post;
-      const float *vb = V + (int64_t)p * J * post + q;
-      float v[JM];
+  for (int rt = 0; rt < RT; ++rt) jc[rt] = min(16 * rt + li, J - 1);
+  f4 acc[2][RT];  // by step parity: independent chains
 #pragma unroll
-      for (int j = 0; j < JM; ++j) v[j] = j < J ? vb[(int64_t)j * post] : 0.f;
+  for (int a = 0; a < 2; ++a)
 #pragma unroll
-      for (int j = 0; j < JM; ++j)
-        if (j < J) Vs[j * tc + tt] = v[j];
-    }
-    __syncthreads();
-    if (!active) continue;
-    int tt = lane;
-    int p = (t0 + lane) / post, q = (t0 + lane) - ((t0 + lane) / post) * post;
-    while (tt < tn) {
-      float u[4];
-      int vo[4];
+    for (int rt = 0; rt < RT; ++rt) acc[a][rt] = f4{0.f, 0.f, 0.f, 0.f};
+  constexpr int kS = 8;
+  for (int s0 = wave * per; s0 < s1; s0 += kS) {
+    float u[kS], v[kS][RT];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const bool ok = tt + 64 * k < tn;
-        u[k] = ok ? U[((int64_t)p * I + i) * post + q] : 0.f;
-        vo[k] = ok ? tt + 64 * k : 0;
-        p += dp;
-        q += dq;
-        if (q >= post) {
-          q -= post;
-          ++p;
-        }
+    for (int k = 0; k < kS; ++k) {
+      const int t = 4 * (s0 + k) + lg;
+      const bool ok = s0 + k < s1 && t < total;
+      const int tt = ok ? t : 0, p = qdiv(tt, inv_post), q = tt - p * post;
+      u[k] = U[((int64_t)p * I + ir) * post + q];
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) v[k][rt] = V[(p * J + jc[rt]) * post + q];
+      if (!ok) {
+        u[k] = 0.f;
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) v[k][rt] = 0.f;
       }
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-#pragma unroll
-        for (int j = 0; j < JM; ++j)
-          if (j < J) acc[j] = fmaf(u[k], Vs[j * tc + vo[k]], acc[j]);
-      }
-      tt += 256;
     }
+#pragma unroll
+    for (int k = 0; k < kS; ++k)
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+        acc[k & 1][rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(u[k], v[k][rt], acc[k & 1][rt], 0, 0, 0);
   }
-  if (!active) return;
 #pragma unroll
-  for (int j = 0; j < JM; ++j) {
+  for (int rt = 0; rt < RT; ++rt) part[wave][rt][lane] = acc[0][rt] + acc[1][rt];
+  __syncthreads();
+  if (wave >= RT) return;
+  f4 sum = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int m = 32; m > 0; m >>= 1) acc[j] += __shfl_xor(acc[j], m, 64);
-  }
-  if (lane < J) {
-    float v = 0.f;
+  for (int w = 0; w < kCeWaves; ++w) sum += part[w][wave][lane];
+  const int j = 16 * wave + li;
 #pragma unroll
-    for (int j = 0; j < JM; ++j)
-      if (j == lane) v = acc[j];
-    out[i * J + lane] = v;
+  for (int k = 0; k < 4; ++k) {
+    const int64_t i = i0 + 4 * lg + k;
+    if (i < I && j < J) out[i * J + j] = sum[k];
   }
 }
 
@@ -428,18 +415,14 @@ nnc_status launch_contract_except(const float *U, const float *V, int64_t pre, i
     NNC_HIP(hipGetLastError());
     return NNC_OK;
   }
-  if (J <= 32 && pre * J * post < INT32_MAX && I < ((int64_t)1 << 31) / 64) {
-    const int grid = (int)((I + 3) / 4);
-#define NNC_CE_ROWS(JM)                                                                              \
-  hipLaunchKernelGGL(contract_except_rows_k<JM>, dim3(grid), dim3(256), 0, s, U, V, (int)pre, I, (int)J, \
-                     (int)post, out)
-    if (J <= 8)
-      NNC_CE_ROWS(8);
-    else if (J <= 16)
-      NNC_CE_ROWS(16);
+  if (J <= 32 && pre * J * post < INT32_MAX && pre * post < (1 << 22) && I < ((int64_t)1 << 31) / 64) {
+    const int grid = (int)((I + 15) / 16);
+    if (J <= 16)
+      hipLaunchKernelGGL(contract_except_rows_k<1>, dim3(grid), dim3(64 * kCeWaves), 0, s, U, V, (int)pre, I, (int)J,
+                         (int)post, out);
     else
-      NNC_CE_ROWS(32);
-#undef NNC_CE_ROWS
+      hipLaunchKernelGGL(contract_except_rows_k<2>, dim3(grid), dim3(64 * kCeWaves), 0, s, U, V, (int)pre, I, (int)J,
+                         (int)post, out);
     NNC_HIP(hipGetLastError());
     return NNC_OK;
   }

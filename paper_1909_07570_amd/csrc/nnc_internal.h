@@ -152,11 +152,12 @@ nnc_status launch_fill_f32(float *x, int64_t n, float v, hipStream_t s);
 // ------------------------------------------------------------------ ls_kernels.hip
 // Least-squares factor step of the real Tucker fit (two launches): A* = num K^{-1}, Cholesky
 // QR A* = Q L^T, A <- Q (num and A distinct), T <- K^{-1} L^{-T} (R x R doubles),
-// Lf <- L (R x R floats, for the core's G x_n L^T), S_out <- Q^T Q.  Pivots of K or of
-// A*^T A* that are not positive are counted in *fails.  R <= 32.  K == nullptr: A* = num,
-// the orthonormalization of a given factor alone.
-nnc_status launch_ls_factor(const float *num, const float *K, int64_t N, int64_t R, float *A,
-                            double *T, float *Lf, float *S_out, unsigned long long *fails, hipStream_t s);
+// Lf <- L (R x R floats), S_out <- Q^T Q, and G <- G x_n L^T in place (G: pre x R x post).
+// Pivots of K or of A*^T A* that are not positive are counted in *fails.  R <= 32.
+// K == nullptr: A* = num, the orthonormalization of a given factor alone.
+nnc_status launch_ls_factor(const float *num, const float *K, int64_t N, int64_t R, float *A, double *T, float *Lf,
+                            float *S_out, float *G, int64_t pre, int64_t post, unsigned long long *fails,
+                            hipStream_t s);
 // Sinv[k] = S[k]^{-1} for k < d (R[k] x R[k] floats, every R[k] <= 32), one launch.
 nnc_status launch_ls_inverses(int d, const int64_t *R, float *const *S, float *const *Sinv,
                               unsigned long long *fails, hipStream_t s);
