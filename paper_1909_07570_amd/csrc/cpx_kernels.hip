@@ -428,6 +428,42 @@ static __device__ inline float dot4(float4 a, float4 b, float s) {
   return fmaf(a.w, b.w, s);
 }
 
+// red[2 b], red[2 b + 1] <- ||A - W H||^2, ||A||^2 in FP64 of the workgroup's problem, if asked for
+// (a barrier inside; every thread takes part)
+static __device__ inline void nmf_residual(const float *A, int as, const float *W, int ws, const float *H, int hs, int N, int r, int m,
+                                           int b, double *red, double (*dred)[kNmfThreads / 64]) {
+  if (!red) return;
+  const int tid = threadIdx.x;
+  double se = 0.0, sa = 0.0;
+  for (int e = tid; e < N * r; e += kNmfThreads) {
+    const int i = e / r, q = e - (e / r) * r;
+    float x = 0.f;
+    for (int k = 0; k < m; ++k) x = fmaf(W[i * ws + k], H[k * hs + q], x);
+    const float av = A[i * as + q];
+    const double dlt = (double)av - (double)x;
+    se += dlt * dlt;
+    sa += (double)av * (double)av;
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    se += __shfl_down(se, off);
+    sa += __shfl_down(sa, off);
+  }
+  if ((tid & 63) == 0) {
+    dred[0][tid >> 6] = se;
+    dred[1][tid >> 6] = sa;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    double a = 0.0, c = 0.0;
+    for (int w = 0; w < kNmfThreads / 64; ++w) {
+      a += dred[0][w];
+      c += dred[1][w];
+    }
+    red[2 * b] = a;
+    red[2 * b + 1] = c;
+  }
+}
+
 template <int RC, int MC>
 __global__ __launch_bounds__(kNmfThreads) void nmf_block_k(NmfArgs g) {
   extern __shared__ __attribute__((aligned(16))) float sm[];
@@ -592,39 +628,390 @@ __global__ __launch_bounds__(kNmfThreads) void nmf_block_k(NmfArgs g) {
   for (int e = tid; e < N * m; e += kNmfThreads) Wg[e] = W[(e / m) * mp + e % m];
   for (int e = tid; e < m * r; e += kNmfThreads) Hg[e] = H[(e / r) * rp + e % r];
   if (mine) atomicAdd(&nclip, mine);
-  if (g.red) {  // ||A - W H||^2 and ||A||^2, FP64
-    double se = 0.0, sa = 0.0;
-    for (int e = tid; e < N * r; e += kNmfThreads) {
-      const int i = e / r, q = e - (e / r) * r;
-      float x = 0.f;
-      for (int k = 0; k < m; ++k) x = fmaf(W[i * mp + k], H[k * rp + q], x);
-      const float av = A[i * rp + q];
-      const double dlt = (double)av - (double)x;
-      se += dlt * dlt;
-      sa += (double)av * (double)av;
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-      se += __shfl_down(se, off);
-      sa += __shfl_down(sa, off);
-    }
-    if ((tid & 63) == 0) {
-      dred[0][tid >> 6] = se;
-      dred[1][tid >> 6] = sa;
-    }
-  }
+  nmf_residual(A, rp, W, mp, H, rp, N, r, m, b, g.red, dred);
   __syncthreads();
-  if (tid == 0) {
-    if (nclip) atomicAdd(g.clips, (unsigned long long)nclip);
-    if (g.red) {
-      double a = 0.0, c = 0.0;
-      for (int w = 0; w < kNmfThreads / 64; ++w) {
-        a += dred[0][w];
-        c += dred[1][w];
-      }
-      g.red[2 * b] = a;
-      g.red[2 * b + 1] = c;
+  if (tid == 0 && nclip) atomicAdd(g.clips, (unsigned long long)nclip);
+}
+
+// =====================================================================================
+// The same sweeps on the FP32 matrix cores, for problems whose padded layout fits the LDS: rows to
+// a multiple of 16, ranks to 4 MS and columns to 4 QS (zeros), strides an odd number of quads (16
+// rows' reads from 64 different banks), all known when compiled.  A sweep is five phases:
+//   G = H H^T                                                   (one 16 x 16 tile a wave)
+//   W <- W * (A H^T) / max(W G, eps)                            (16 rows of W a wave at a time)
+//   [W^T W | W^T A] over row ranges                             (NB ranges a wave at a time)
+//   the ranges' sums added in order: G2 to LDS, P to the thread of H's entry
+//   H <- H * P / max(G2 H, eps), into H's other buffer.
+// Each entry of a product is one accumulator's chain in the order of the contracted index, and a
+// 16 x 16 x 4 step adds its four products one after the other: the sums are those of nmf_block_k,
+// bit for bit (the iteration is not contracting: another order moves the result of a few hundred
+// sweeps by more than rounding).  One quad of ranks past a multiple of 16 (m = 17 .. 20) has its
+// part of the W step on the VALU, a value a lane, instead of a second tile of three quarters zeros.
+// Bound: instruction issue and latency in one CU: three 512 x 10 at m = 20, 8.7 us a sweep in this
+// form, 26.5 in nmf_block_k.
+// =====================================================================================
+constexpr int kNmfWaves = kNmfThreads / 64;
+
+template <int MS, int QS>
+struct NmfMM {
+  static constexpr int odd4(int q) { return 4 * (q | 1); }
+  static constexpr int M = 4 * MS, Q = 4 * QS, ms = odd4(MS), rs = odd4(QS), os = odd4(MS + QS);
+  static constexpr int H = M * rs;            // one of H's two buffers
+  static constexpr int dump = 4 * ms + 64;    // values of padded ranks go here
+  static size_t floats(int rows, int m) {
+    const size_t n16 = (rows + 15) & ~15;
+    return n16 * (rs + ms) + 2 * H + M * ms + dump + (size_t)nmf_splits(m) * m * os;
+  }
+};
+
+template <int MS, int QS>
+__global__ __launch_bounds__(kNmfThreads) void nmf_mm_k(NmfArgs g) {
+  extern __shared__ __attribute__((aligned(16))) float sm[];
+  __shared__ unsigned int nclip;
+  __shared__ int range[kNmfSplitMax + 1];
+  __shared__ double dred[2][kNmfWaves];
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  using L = NmfMM<MS, QS>;
+  constexpr bool kTail = MS % 4 == 1;
+  constexpr int MW = kTail ? MS / 4 : (MS + 3) / 4;  // 16-wide tiles: ranks in the W step, ranks, ranks and columns
+  constexpr int MT = (MS + 3) / 4, CT = (MS + QS + 3) / 4;
+  constexpr int ms = L::ms, rs = L::rs, os = L::os;
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, li = lane & 15, lg = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int N = g.rows[b], m = g.m[b], r = g.cols, S = nmf_splits(m), n16 = (N + 15) & ~15;
+  const float *__restrict__ Ag = g.A[b];
+  float *__restrict__ Wg = g.W[b];
+  float *__restrict__ Hg = g.H[b];
+  float *A = sm, *W = A + n16 * rs, *H0 = W + n16 * ms, *G = H0 + 2 * L::H, *dump = G + L::M * ms, *part = dump + L::dump;
+  auto mfma = [](float x, float y, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, c, 0, 0, 0); };
+  const f4 zero = f4{0.f, 0.f, 0.f, 0.f};
+  for (int e = tid; e < n16 * rs; e += kNmfThreads) {
+    const int i = e / rs, q = e - i * rs;
+    A[e] = i < N && q < r ? Ag[i * r + q] : 0.f;
+  }
+  for (int e = tid; e < n16 * ms; e += kNmfThreads) {
+    const int i = e / ms, k = e - i * ms;
+    W[e] = i < N && k < m ? Wg[i * m + k] : 0.f;
+  }
+  for (int e = tid; e < L::H; e += kNmfThreads) {
+    const int j = e / rs, q = e - j * rs;
+    H0[e] = j < m && q < r ? Hg[j * r + q] : 0.f;
+    H0[L::H + e] = 0.f;
+  }
+  for (int e = tid; e < L::M * ms; e += kNmfThreads) G[e] = 0.f;
+  if (tid <= S) range[tid] = N * tid / S;
+  if (tid == 0) nclip = 0;
+  __syncthreads();
+  unsigned int mine = 0;
+  const double eps = g.eps;
+  float eps_up = (float)eps;  // den < eps in double if and only if den < eps_up: the float at or above it
+  if ((double)eps_up < eps) eps_up = nextafterf(eps_up, INFINITY);
+  const unsigned int lowest = __float_as_uint(fmaxf(eps_up, 1e-37f));  // and normal
+  auto mu = [&](float x, float num, float den, bool valid) {
+    const bool low = den < eps_up;
+    mine += low && valid;
+    return (float)(((double)x * (double)num) / (low ? eps : (double)den));
+  };
+  // the thread's entries of the sums: P's (tid + 512 u < m r), then the upper triangle of G
+  constexpr int kHv = (L::M * L::Q + kNmfThreads - 1) / kNmfThreads;
+  constexpr int kSv = (L::M * L::Q + L::M * (L::M + 1) / 2 + kNmfThreads - 1) / kNmfThreads;
+  const int mr = m * r;
+  int sum_at[kSv], sum_j[kSv], sum_c[kSv];  // its place, row and column
+#pragma unroll
+  for (int u = 0; u < kSv; ++u) {
+    const int e = tid + u * kNmfThreads;
+    sum_at[u] = -1;
+    sum_j[u] = sum_c[u] = 0;
+    if (e < mr) {
+      sum_j[u] = e / r;
+      sum_c[u] = e - sum_j[u] * r;
+      sum_at[u] = sum_j[u] * os + L::M + sum_c[u];
+    } else if (e < mr + m * (m + 1) / 2) {
+      int t = e - mr, j = 0;
+      while (t >= m - j) t -= m - j++;
+      sum_j[u] = j;
+      sum_c[u] = j + t;
+      sum_at[u] = j * os + j + t;
     }
   }
+  const float *col[CT];  // the lane's columns of [W | A]
+  int by[CT];            // and how far apart their rows are
+#pragma unroll
+  for (int c = 0; c < CT; ++c) {
+    const int o = 16 * c + li;
+    col[c] = (o < L::M ? W + o : A + min(o - L::M, rs - 1)) + lg * (o < L::M ? ms : rs);
+    by[c] = o < L::M ? ms : rs;
+  }
+  for (int it = 0; it < g.iters; ++it) {
+    const float *H = H0 + (it & 1) * L::H;
+    float *Hn = H0 + ((it & 1) ^ 1) * L::H;
+    // ---- G = H H^T (H's rows past 4 MS: other parts of the LDS, for rows and columns that are not stored)
+    if (wave < MT * MT) {
+      const int ma = wave / MT, mb = wave % MT;
+      const float *ha = H + (16 * ma + li) * rs + lg, *hb = H + (16 * mb + li) * rs + lg;
+      f4 acc = zero;
+#pragma unroll
+      for (int s = 0; s < QS; ++s) acc = mfma(ha[4 * s], hb[4 * s], acc);
+      if (16 * mb + li < L::M) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (16 * ma + 4 * lg < L::M) G[(16 * ma + 4 * lg + k) * ms + 16 * mb + li] = acc[k];
+      }
+    }
+    __syncthreads();
+    // ---- W
+    {
+      f4 th[kTail ? QS : 1], tg[kTail ? MS : 1];
+      const int tj = 16 * MW + (lane & 3);  // the lane's rank of the tail, its row: lane / 4
+      float h[QS][MW], gg[MS][MW];
+#pragma unroll
+      for (int mt = 0; mt < MW; ++mt) {
+#pragma unroll
+        for (int s = 0; s < QS; ++s) h[s][mt] = H[(16 * mt + li) * rs + 4 * s + lg];
+#pragma unroll
+        for (int s = 0; s < MS; ++s) gg[s][mt] = G[(16 * mt + li) * ms + 4 * s + lg];  // G is symmetric
+      }
+      if (kTail) {
+#pragma unroll
+        for (int s = 0; s < QS; ++s) th[kTail ? s : 0] = *reinterpret_cast<const f4 *>(H + tj * rs + 4 * s);
+#pragma unroll
+        for (int s = 0; s < MS; ++s) tg[kTail ? s : 0] = *reinterpret_cast<const f4 *>(G + tj * ms + 4 * s);
+      }
+      for (int t = wave; 16 * t < N; t += kNmfWaves) {
+        constexpr int NQ = 4 * MW + (kTail ? 1 : 0);  // the lane's entries of the tile
+        const int rd = 16 * t + 4 * lg;
+        const float *ap = A + (16 * t + li) * rs + lg, *wp = W + (16 * t + li) * ms + lg;
+        float *xp = W + rd * ms + li;
+        float a[QS], w[MS], q_x[NQ], q_num[NQ], q_den[NQ];
+        bool q_in[NQ];
+#pragma unroll
+        for (int s = 0; s < QS; ++s) a[s] = ap[4 * s];
+#pragma unroll
+        for (int s = 0; s < MS; ++s) w[s] = wp[4 * s];
+#pragma unroll
+        for (int u = 0; u < 4 * MW; ++u) q_x[u] = xp[(u & 3) * ms + 16 * (u >> 2)];
+        f4 num[MW], den[MW];
+#pragma unroll
+        for (int mt = 0; mt < MW; ++mt) num[mt] = den[mt] = zero;
+#pragma unroll
+        for (int s = 0; s < (MS > QS ? MS : QS); ++s) {
+          if (s < QS) {
+#pragma unroll
+            for (int mt = 0; mt < MW; ++mt) num[mt] = mfma(a[s < QS ? s : 0], h[s < QS ? s : 0][mt], num[mt]);
+          }
+          if (s < MS) {
+#pragma unroll
+            for (int mt = 0; mt < MW; ++mt) den[mt] = mfma(w[s < MS ? s : 0], gg[s < MS ? s : 0][mt], den[mt]);
+          }
+        }
+        if (kTail) {
+          const int row = 16 * t + (lane >> 2);
+          float tn = 0.f, td = 0.f;
+#pragma unroll
+          for (int s = 0; s < QS; ++s) {
+            const f4 v = *reinterpret_cast<const f4 *>(A + row * rs + 4 * s);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) tn = fmaf(v[u], th[kTail ? s : 0][u], tn);
+          }
+#pragma unroll
+          for (int s = 0; s < MS; ++s) {
+            const f4 v = *reinterpret_cast<const f4 *>(W + row * ms + 4 * s);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) td = fmaf(v[u], tg[kTail ? s : 0][u], td);
+          }
+          q_x[NQ - 1] = W[row * ms + tj];
+          q_num[NQ - 1] = tn;
+          q_den[NQ - 1] = td;
+          q_in[NQ - 1] = tj < m && row < N;
+        }
+#pragma unroll
+        for (int u = 0; u < 4 * MW; ++u) {
+          q_num[u] = num[u >> 2][u & 3];
+          q_den[u] = den[u >> 2][u & 3];
+          q_in[u] = 16 * (u >> 2) + li < m && rd + (u & 3) < N;
+        }
+        // All quotients of the lane at once, a step of every chain after the other (one by one they are a
+        // serial chain of ten FP64 operations each).  The reciprocal is the hardware's estimate and two
+        // Newton steps, within an ulp or two of double precision, so the float is the one of a division
+        // except where that lies within 2^-28 of its own rounding boundary; a division sequence takes 85
+        // cycles of a wave, this 21 (512 threads, eight independent quotients each).  Denominators to
+        // clip, subnormal, infinite or NaN take the division.
+        bool odd = false;
+#pragma unroll
+        for (int u = 0; u < NQ; ++u) odd |= q_in[u] && __float_as_uint(q_den[u]) - lowest > 0x7f7fffffu - lowest;
+        float v[NQ];
+        if (__any(odd)) {
+#pragma unroll
+          for (int u = 0; u < NQ; ++u) v[u] = mu(q_x[u], q_num[u], q_den[u], q_in[u]);
+        } else {
+          double q[NQ];
+#pragma unroll
+          for (int u = 0; u < NQ; ++u) q[u] = __builtin_amdgcn_rcp((double)q_den[u]);
+#pragma unroll
+          for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int u = 0; u < NQ; ++u) q[u] = fma(q[u], fma(-(double)q_den[u], q[u], 1.0), q[u]);
+#pragma unroll
+          for (int u = 0; u < NQ; ++u) v[u] = (float)(((double)q_x[u] * (double)q_num[u]) * q[u]);
+        }
+        // rows past N may hold anything, ranks past m stay zero
+#pragma unroll
+        for (int mt = 0; mt < MW; ++mt) {
+          float *to = 16 * mt + li < m ? xp + 16 * mt : dump + lane;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) to[k * ms] = v[4 * mt + k];
+        }
+        if (kTail) *(tj < m ? W + (16 * t + (lane >> 2)) * ms + tj : dump + lane) = v[NQ - 1];
+      }
+    }
+    __syncthreads();
+    // ---- [W^T W | W^T A] of the row ranges, whose lengths differ by at most one
+    constexpr int NB = MT * CT <= 4 ? 4 : MT * CT <= 6 ? 2 : 1;
+    for (int sp0 = wave; sp0 < S; sp0 += NB * kNmfWaves) {
+      f4 acc[NB][MT][CT];
+      const float *xp[NB], *yp[NB][CT];
+      int left[NB];  // rows of the range from the lane's row of the step
+#pragma unroll
+      for (int n = 0; n < NB; ++n) {
+        const int sp = min(sp0 + n * kNmfWaves, S - 1), i0 = __builtin_amdgcn_readfirstlane(range[sp]);
+        left[n] = __builtin_amdgcn_readfirstlane(range[sp + 1]) - i0 - lg;
+        xp[n] = W + (i0 + lg) * ms + li;
+#pragma unroll
+        for (int c = 0; c < CT; ++c) yp[n][c] = col[c] + i0 * by[c];
+      }
+      float x[NB][MT], y[NB][CT];
+      auto load = [&] {
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+#pragma unroll
+          for (int p = 0; p < MT; ++p) x[n][p] = xp[n][16 * p];
+#pragma unroll
+          for (int c = 0; c < CT; ++c) y[n][c] = *yp[n][c];
+          xp[n] += 4 * ms;
+#pragma unroll
+          for (int c = 0; c < CT; ++c) yp[n][c] += 4 * by[c];
+        }
+      };
+      auto step = [&](bool first, bool whole) {  // four rows of each range, the next four on their way
+        float u[NB][MT], v[NB][CT];
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+          const unsigned int in = whole || left[n] > 0 ? 0xffffffffu : 0u;  // rows past the range are others of the LDS
+#pragma unroll
+          for (int p = 0; p < MT; ++p) u[n][p] = __uint_as_float(__float_as_uint(x[n][p]) & in);
+#pragma unroll
+          for (int c = 0; c < CT; ++c) v[n][c] = __uint_as_float(__float_as_uint(y[n][c]) & in);
+          left[n] -= 4;
+        }
+        load();
+#pragma unroll
+        for (int p = 0; p < MT; ++p)
+#pragma unroll
+          for (int c = p; c < CT; ++c)
+#pragma unroll
+            for (int n = 0; n < NB; ++n) acc[n][p][c] = mfma(u[n][p], v[n][c], first ? zero : acc[n][p][c]);
+      };
+      const int whole = N / S & ~3;
+      int i = 4;
+      load();
+      step(true, whole > 0);
+      for (; i + 8 <= whole; i += 8) {
+        step(false, true);
+        step(false, true);
+      }
+      for (; i < whole; i += 4) step(false, true);
+      for (; i < (N + S - 1) / S; i += 4) step(false, false);
+#pragma unroll
+      for (int n = 0; n < NB; ++n) {
+        const int sp = sp0 + n * kNmfWaves;
+        if (sp < S) {
+          float *pw = part + sp * m * os + 4 * lg * os + li;
+#pragma unroll
+          for (int p = 0; p < MT; ++p)
+#pragma unroll
+            for (int c = p; c < CT; ++c)
+#pragma unroll
+              for (int k = 0; k < 4; ++k) {
+                const bool in = 16 * p + 4 * lg + k < m && 16 * c + li < L::M + L::Q;
+                float *to = in ? pw + (16 * p + k) * os + 16 * c : dump + lane;
+                *to = acc[n][p][c][k];
+              }
+        }
+      }
+    }
+    __syncthreads();
+    // ---- the ranges' sums in order
+    float pv[kHv];
+#pragma unroll
+    for (int u = 0; u < kSv; ++u)
+      if (sum_at[u] >= 0) {
+        const float *pp = part + sum_at[u];
+        float t = *pp;
+#pragma unroll 8
+        for (int sp = 1; sp < S; ++sp) t += pp[sp * m * os];
+        if (u < kHv && tid + u * kNmfThreads < mr) {
+          pv[u < kHv ? u : 0] = t;
+        } else {
+          G[sum_j[u] * ms + sum_c[u]] = t;
+          G[sum_c[u] * ms + sum_j[u]] = t;
+        }
+      }
+    __syncthreads();
+    // ---- H
+#pragma unroll
+    for (int u = 0; u < kHv; ++u)
+      if (tid + u * kNmfThreads < mr) {
+        const int at = sum_j[u] * rs + sum_c[u];
+        float den = 0.f;
+#pragma unroll
+        for (int k = 0; k < L::M; k += 4) {
+          const f4 gk = *reinterpret_cast<const f4 *>(G + sum_j[u] * ms + k);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) den = fmaf(gk[v], H[(k + v) * rs + sum_c[u]], den);
+        }
+        Hn[at] = mu(H[at], pv[u], den, true);
+      }
+    __syncthreads();
+  }
+  const float *H = H0 + (g.iters & 1) * L::H;
+  for (int e = tid; e < N * m; e += kNmfThreads) Wg[e] = W[(e / m) * ms + e % m];
+  for (int e = tid; e < m * r; e += kNmfThreads) Hg[e] = H[(e / r) * rs + e % r];
+  if (mine) atomicAdd(&nclip, mine);
+  nmf_residual(A, rs, W, ms, H, rs, N, r, m, b, g.red, dred);
+  __syncthreads();
+  if (tid == 0 && nclip) atomicAdd(g.clips, (unsigned long long)nclip);
+}
+
+// The forms of nmf_mm_k: ranks up to 16, 20, 24 or 32 by columns up to 8, 12, 16 or 32.
+#define NNC_NMF_ALL                                         \
+  NNC_NMF(4, 2) NNC_NMF(4, 3) NNC_NMF(4, 4) NNC_NMF(4, 8)   \
+  NNC_NMF(5, 2) NNC_NMF(5, 3) NNC_NMF(5, 4) NNC_NMF(5, 8)   \
+  NNC_NMF(6, 2) NNC_NMF(6, 3) NNC_NMF(6, 4) NNC_NMF(6, 8)   \
+  NNC_NMF(8, 2) NNC_NMF(8, 3) NNC_NMF(8, 4) NNC_NMF(8, 8)
+
+// Launches the form that holds the largest rank and the columns; false where a problem's padded
+// layout does not fit the LDS (many rows), which nmf_block_k with its packed rows then takes.
+static bool launch_nmf_mm(const NmfArgs &g, int n, int mmax, hipStream_t s, nnc_status *st) {
+  const int ms = mmax <= 16 ? 4 : mmax <= 20 ? 5 : mmax <= 24 ? 6 : 8;
+  const int qs = g.cols <= 8 ? 2 : g.cols <= 12 ? 3 : g.cols <= 16 ? 4 : 8;
+  size_t lds = 0;
+#define NNC_NMF(MSV, QSV)        \
+  if (ms == MSV && qs == QSV)    \
+    for (int b = 0; b < n; ++b) lds = std::max(lds, NmfMM<MSV, QSV>::floats(g.rows[b], g.m[b]) * 4);
+  NNC_NMF_ALL
+#undef NNC_NMF
+  if (lds > kNmfLdsMax) return false;
+  auto run = [&](auto *kernel) -> nnc_status {
+    NNC_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kNmfLdsMax));
+    hipLaunchKernelGGL(kernel, dim3(n), dim3(kNmfThreads), lds, s, g);
+    NNC_HIP(hipGetLastError());
+    return NNC_OK;
+  };
+#define NNC_NMF(MSV, QSV) \
+  if (ms == MSV && qs == QSV) *st = run(nmf_mm_k<MSV, QSV>);
+  NNC_NMF_ALL
+#undef NNC_NMF
+  return true;
 }
 
 nnc_status launch_nmf_block(int n, const float *const *A, const int *rows, int cols, const int *m,
@@ -650,6 +1037,8 @@ nnc_status launch_nmf_block(int n, const float *const *A, const int *rows, int c
   g.red = red;
   int mmax = 1;
   for (int k = 0; k < n; ++k) mmax = std::max(mmax, m[k]);
+  nnc_status st = NNC_OK;
+  if (launch_nmf_mm(g, n, mmax, s, &st)) return st;
   const int RC = cols <= 8 ? 8 : (cols <= 16 ? 16 : 32), MC = mmax <= 8 ? 8 : (mmax <= 16 ? 16 : 32);
 #define NNC_NMF(RCV, MCV)                                                                         \
   do {                                                                                            \
