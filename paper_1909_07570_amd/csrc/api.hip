@@ -922,7 +922,7 @@ struct CpxPlan {
   int d = 0, r = 0;
   int64_t N[kMaxDim];
   int64_t size = 0;
-  size_t oZ, oT, oM, oPart, oWA, oWC, oS, oClip, oFlag, oRed, oRpart, total;
+  size_t oZ, oT, oPart, oWA, oWC, oS, oClip, oFlag, oRed, oRpart, total;
 };
 
 static CpxPlan plan_cpx(int d, const int64_t *dims, int r) {
@@ -930,11 +930,8 @@ static CpxPlan plan_cpx(int d, const int64_t *dims, int r) {
   p.d = d;
   p.r = r;
   p.size = prod(dims, 0, d);
-  int64_t maxN = 1, part = 0, wa = 0, wc = 0;
-  for (int k = 0; k < d; ++k) {
-    p.N[k] = dims[k];
-    maxN = std::max(maxN, dims[k]);
-  }
+  int64_t part = 0, wa = 0, wc = 0;
+  for (int k = 0; k < d; ++k) p.N[k] = dims[k];
   for (int n = 0; n < d - 1; ++n) {  // modes served by Z
     const int64_t A = prod(dims, 0, n), C = prod(dims, n + 1, d - 1);
     part = std::max(part, diag_part_floats(A, dims[n], C, r));
@@ -949,7 +946,6 @@ static CpxPlan plan_cpx(int d, const int64_t *dims, int r) {
   Layout L;
   p.oZ = L.take(sizeof(float) * (size_t)(p.size / dims[d - 1] * r));  // also the residual's rows
   p.oT = L.take(sizeof(float) * (size_t)(p.size / dims[0] * r));
-  p.oM = L.take(sizeof(float) * (size_t)(maxN * r));
   p.oPart = L.take(sizeof(float) * (size_t)part);
   p.oWA = L.take(sizeof(float) * (size_t)wa);
   p.oWC = L.take(sizeof(float) * (size_t)wc);
@@ -991,27 +987,35 @@ static nnc_status kr_weights(float *const *B, const int64_t *N, int lo, int hi, 
 static nnc_status cpx_sweep(const CpxPlan &p, char *base, const void *X, nnc_dtype dt, float *const *B,
                             double eps, hipStream_t s) {
   const int d = p.d, r = p.r;
-  float *Z = (float *)(base + p.oZ), *T = (float *)(base + p.oT), *M = (float *)(base + p.oM);
+  float *Z = (float *)(base + p.oZ), *T = (float *)(base + p.oT);
   float *part = (float *)(base + p.oPart), *WA = (float *)(base + p.oWA), *WC = (float *)(base + p.oWC);
   float *S = (float *)(base + p.oS);
   unsigned long long *clips = (unsigned long long *)(base + p.oClip);
+  // One mode: its partial MTTKRP beside the Gram of the mode updated before it (which only the update
+  // reads; the first sweep's first is the Gram that the fit started with), then the update.  Factors
+  // whose Gram that launch does not take have it formed after their update.
+  auto mode = [&](int n, const float *Y, int rho_first, int64_t A, int64_t C, const float *wa, const float *wc) -> nnc_status {
+    const int b = (n + d - 1) % d;
+    const bool beside = diag_gram_fits(p.N[b], r);
+    NNC_TRY(launch_diag(Y, rho_first, A, p.N[n], C, wa, wc, r, part, beside ? B[b] : nullptr, p.N[b],
+                        S + (size_t)b * r * r, s));
+    NNC_TRY(launch_cp_mu(B[n], part, diag_slices(A, p.N[n], C), S, d, n, p.N[n], r, eps, clips, s));
+    if (diag_gram_fits(p.N[n], r)) return NNC_OK;
+    return launch_gram_block(B[n], p.N[n], r, S + (size_t)n * r * r, s);
+  };
   NNC_TRY(launch_ttm(X, dt, p.size / p.N[d - 1], p.N[d - 1], 1, B[d - 1], r, 1, r, Z, s, true));
   for (int n = 0; n < d - 1; ++n) {
     const float *wa, *wc;
     int64_t A, C;
     NNC_TRY(kr_weights(B, p.N, 0, n, r, WA, &wa, &A, s));
     NNC_TRY(kr_weights(B, p.N, n + 1, d - 1, r, WC, &wc, &C, s));
-    NNC_TRY(launch_diag(Z, 0, A, p.N[n], C, wa, wc, r, M, part, s));
-    NNC_TRY(launch_cp_mu(B[n], M, S, d, n, p.N[n], r, eps, clips, s));
-    NNC_TRY(launch_gram_block(B[n], p.N[n], r, S + (size_t)n * r * r, s));
+    NNC_TRY(mode(n, Z, 0, A, C, wa, wc));
   }
   NNC_TRY(launch_ttm(X, dt, 1, p.N[0], p.size / p.N[0], B[0], r, 1, r, T, s, true));
   const float *wa;
   int64_t A;
   NNC_TRY(kr_weights(B, p.N, 1, d - 1, r, WA, &wa, &A, s));
-  NNC_TRY(launch_diag(T, 1, A, p.N[d - 1], 1, wa, nullptr, r, M, part, s));
-  NNC_TRY(launch_cp_mu(B[d - 1], M, S, d, d - 1, p.N[d - 1], r, eps, clips, s));
-  NNC_TRY(launch_gram_block(B[d - 1], p.N[d - 1], r, S + (size_t)(d - 1) * r * r, s));
+  NNC_TRY(mode(d - 1, T, 1, A, 1, wa, nullptr));
   return NNC_OK;
 }
 

@@ -25,9 +25,85 @@ struct DiagArgs {
   int64_t A, Nt, C;
   int r;
   int rho_first;
-  float *out;    // [Nt][r] (one slice) or partials [slices][Nt][r]
+  float *out;  // [slices][Nt][r]
   int slices;
+  // block 0 forms the Gram gS = gB^T gB (gN x r) of another factor, if gB is not null
+  const float *gB;
+  float *gS;
+  int gN;
 };
+
+constexpr int kGramSums = 1024;  // partial sums of a Gram: 1024 / r^2 row sets times its entries
+
+// S = B^T B (N x r, r <= 16 TR) by a block of kDiagThreads threads with the sums of gram_block_k, bit for
+// bit: entry e of row set k (rows j with j mod sets == k, ascending) is one FP32 accumulator, whose
+// 16 x 16 x 4 MFMA adds four rows one after the other, and the sets are added in order.  NB sets of a
+// wave run side by side; a lane's row of a step is both operands.
+template <int TR>
+static __device__ inline void gram_sets(const float *__restrict__ B, int N, int r, float *__restrict__ S, float *part) {
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  constexpr int kW = kDiagThreads / 64, NB = 4;
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lg = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rr = r * r, sets = kGramSums / rr;
+  const int steps = ((N + sets - 1) / sets + 3) / 4;
+  for (int k0 = wave; k0 < sets; k0 += NB * kW) {
+    f4 acc[NB][TR][TR];
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+#pragma unroll
+      for (int p = 0; p < TR; ++p)
+#pragma unroll
+        for (int q = 0; q < TR; ++q) acc[n][p][q] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int s = 0; s < steps; ++s) {
+      float x[NB][TR];
+#pragma unroll
+      for (int n = 0; n < NB; ++n) {
+        const int row = k0 + n * kW + (4 * s + lg) * sets;  // sets past the last are not stored
+#pragma unroll
+        for (int p = 0; p < TR; ++p) {
+          const float v = B[min(row, N - 1) * r + min(16 * p + li, r - 1)];
+          x[n][p] = row < N ? v : 0.f;
+        }
+      }
+#pragma unroll
+      for (int p = 0; p < TR; ++p)
+#pragma unroll
+        for (int q = 0; q < TR; ++q)
+#pragma unroll
+          for (int n = 0; n < NB; ++n)
+            acc[n][p][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[n][p], x[n][q], acc[n][p][q], 0, 0, 0);
+    }
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+#pragma unroll
+      for (int p = 0; p < TR; ++p)
+#pragma unroll
+        for (int q = 0; q < TR; ++q)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int a = 16 * p + 4 * lg + j, b = 16 * q + li, k = k0 + n * kW;
+            if (a < r && b < r && k < sets) part[k * rr + a * r + b] = acc[n][p][q][j];
+          }
+  }
+  __syncthreads();
+  for (int e = tid; e < rr; e += kDiagThreads) {
+    float t = part[e];
+    for (int k = 1; k < sets; ++k) t += part[k * rr + e];
+    S[e] = t;
+  }
+}
+
+// Block 0 of a launch with a Gram: true where the caller is done.  part: the block's LDS, at least
+// kGramSums floats.
+template <int RM>
+static __device__ inline bool diag_gram(const DiagArgs &g, float *part) {
+  static_assert(kDiagThreads * RM >= kGramSums, "the Gram's sums fit the block's LDS");
+  if (!g.gB || blockIdx.x) return false;
+  gram_sets<(RM + 15) / 16>(g.gB, g.gN, g.r, g.gS, part);
+  return true;
+}
 
 static __device__ inline float diag_y(const DiagArgs &g, int64_t a, int64_t i, int64_t c, int rho) {
   const int64_t e = (a * g.Nt + i) * g.C + c;
@@ -48,9 +124,10 @@ template <int RM>
 __global__ __launch_bounds__(kDiagThreads) void diag_inner_k(DiagArgs g) {
   static_assert(kDiagThreads == 256, "the tree below has two cross-wave steps");
   __shared__ float red[kDiagThreads * RM];
-  const int t = threadIdx.x;
-  const int64_t i = blockIdx.x % g.Nt;
-  const int s = (int)(blockIdx.x / g.Nt);
+  if (diag_gram<RM>(g, red)) return;
+  const int t = threadIdx.x, block = blockIdx.x - (g.gB ? 1 : 0);
+  const int64_t i = block % g.Nt;
+  const int s = (int)(block / g.Nt);
   const int64_t F = g.A * g.C;
   const int64_t f0 = F * s / g.slices, f1 = F * (s + 1) / g.slices;
   float acc[RM];
@@ -98,9 +175,11 @@ __global__ __launch_bounds__(kDiagThreads) void diag_inner_k(DiagArgs g) {
 template <int RM>
 __global__ __launch_bounds__(kDiagThreads) void diag_outer_k(DiagArgs g) {
   __shared__ float red[kDiagThreads * RM];
+  if (diag_gram<RM>(g, red)) return;
+  const int block = blockIdx.x - (g.gB ? 1 : 0);
   const int64_t tiles = (g.Nt + 63) / 64;
-  const int64_t tile = blockIdx.x % tiles;
-  const int s = (int)(blockIdx.x / tiles);
+  const int64_t tile = block % tiles;
+  const int s = (int)(block / tiles);
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t i = tile * 64 + lane;
   const int64_t ic = i < g.Nt ? i : g.Nt - 1;
@@ -151,25 +230,6 @@ __global__ __launch_bounds__(kDiagThreads) void diag_outer_k(DiagArgs g) {
     g.out[((int64_t)s * g.Nt + ii) * g.r + q] = t;
   }
 }
-// out[e] = sum_{s < slices} part[s][e], s in order.
-__global__ void diag_sum_k(const float *__restrict__ part, int slices, int64_t n, float *__restrict__ out) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n) return;
-  // slices in order; the loads of a group of kB are all in flight before the adds
-  constexpr int kB = 16;
-  float t = part[e];
-  int s = 1;
-  for (; s + kB <= slices; s += kB) {
-    float v[kB];
-#pragma unroll
-    for (int k = 0; k < kB; ++k) v[k] = part[(int64_t)(s + k) * n + e];
-#pragma unroll
-    for (int k = 0; k < kB; ++k) t += v[k];
-  }
-  for (; s < slices; ++s) t += part[(int64_t)s * n + e];
-  out[e] = t;
-}
-
 int64_t diag_slices(int64_t A, int64_t Nt, int64_t C) {
   if (C > 1) {
     const int64_t per = std::max<int64_t>(1, 512 / Nt);
@@ -180,13 +240,18 @@ int64_t diag_slices(int64_t A, int64_t Nt, int64_t C) {
   return std::max<int64_t>(1, std::min<int64_t>(per, A / 16));
 }
 
+// A Gram by the diagonal contraction's extra block takes about as long as the contraction up to here
+// (512 rows at rank 10: hidden; gram_block_k 5.1 us); below rank 4 most of its tiles would be padding.
+bool diag_gram_fits(int64_t N, int r) { return N <= 1024 && r >= 4; }
+
 nnc_status launch_diag(const float *Y, int rho_first, int64_t A, int64_t Nt, int64_t C, const float *WA,
-                       const float *WC, int r, float *out, float *part, hipStream_t s) {
+                       const float *WC, int r, float *part, const float *gB, int64_t gN, float *gS, hipStream_t s) {
   if (r < 1 || r > 32) return fail(NNC_EUNSUPPORTED, "rank %d outside [1, 32]", r);
   const int64_t S = diag_slices(A, Nt, C);
-  if (S > 1 && !part) return fail(NNC_EINVAL, "diag: partial buffer missing");
-  DiagArgs g{Y, WA, WC, A, Nt, C, r, rho_first, S > 1 ? part : out, (int)S};
-  const int64_t blocks = C > 1 ? Nt * S : ((Nt + 63) / 64) * S;
+  if (!part) return fail(NNC_EINVAL, "diag: partial buffer missing");
+  if (gB && !diag_gram_fits(gN, r)) return fail(NNC_EUNSUPPORTED, "diag: Gram of %lld rows at rank %d", (long long)gN, r);
+  DiagArgs g{Y, WA, WC, A, Nt, C, r, rho_first, part, (int)S, gB, gS, (int)gN};
+  const int64_t blocks = (C > 1 ? Nt * S : ((Nt + 63) / 64) * S) + (gB ? 1 : 0);
   if (blocks > 0x7fffffff) return fail(NNC_EUNSUPPORTED, "diag: grid too large");
   const int RM = r <= 8 ? 8 : (r <= 16 ? 16 : 32);
 #define NNC_DIAG(KERN)                                                                         \
@@ -198,27 +263,41 @@ nnc_status launch_diag(const float *Y, int rho_first, int64_t A, int64_t Nt, int
   if (C > 1) NNC_DIAG(diag_inner_k);
   else NNC_DIAG(diag_outer_k);
 #undef NNC_DIAG
-  if (S > 1) {
-    const int64_t n = Nt * r;
-    hipLaunchKernelGGL(diag_sum_k, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, part, (int)S, n, out);
-  }
   NNC_HIP(hipGetLastError());
   return NNC_OK;
 }
 
 int64_t diag_part_floats(int64_t A, int64_t Nt, int64_t C, int r) {
   const int64_t S = diag_slices(A, Nt, C);
-  return S > 1 ? S * Nt * r : 0;
+  return S * Nt * r;
 }
 
-// B <- B * M / max(B H, eps) with H = prod_{k != n} S_k (entrywise, S packed [d][r][r]);
-// FP64 division, clipped denominators counted.  Thread (row, rho), 256 / r rows per block.
-__global__ __launch_bounds__(256) void cp_mu_k(float *__restrict__ B, const float *__restrict__ M,
+// B <- B * M / max(B H, eps) with M = sum_{s < slices} part[s] (s in order) and H = prod_{k != n} S_k
+// (entrywise, S packed [d][r][r]); FP64 division, clipped denominators counted.  Thread (row, rho),
+// 256 / r rows per block.  Bound by the latency of one round of loads: 4.8 us at 512 x 10 and 64 slices
+// (the sum and the update as two launches: 10.0).
+__global__ __launch_bounds__(256) void cp_mu_k(float *__restrict__ B, const float *__restrict__ part, int slices,
                                                const float *__restrict__ S, int d, int n, int64_t N,
                                                int r, double eps, unsigned long long *clips) {
   __shared__ float H[32 * 32];
   __shared__ unsigned int nclip;
   const int tid = threadIdx.x;
+  const int rpb = 256 / r;
+  const int64_t i = (int64_t)blockIdx.x * rpb + tid / r;
+  const int q = tid % r;
+  const bool act = tid < rpb * r && i < N;
+  // the loads of a group of slices are all in flight before the adds, the first group's (and the row's)
+  // beside those of H; a slice past the last is read as the last and added as zero
+  constexpr int kB = 32, kR = 8;
+  const int64_t n1 = N * r;
+  const float *pe = part + (act ? i * r + q : 0);
+  float v[kB], row[kR];
+#pragma unroll
+  for (int k = 0; k < kB; ++k) v[k] = pe[(int64_t)min(k, slices - 1) * n1];
+  const float *br = B + (act ? i * r : 0);
+#pragma unroll
+  for (int t = 0; t < kR; ++t) row[t] = br[min(t, r - 1)];
+  const float old = br[act ? q : 0];
   for (int e = tid; e < r * r; e += 256) {
     float h = 1.f;
     for (int k = 0; k < d; ++k)
@@ -226,22 +305,30 @@ __global__ __launch_bounds__(256) void cp_mu_k(float *__restrict__ B, const floa
     H[e] = h;
   }
   if (tid == 0) nclip = 0;
+  float m = v[0];
+#pragma unroll
+  for (int k = 1; k < kB; ++k) m += k < slices ? v[k] : 0.f;
+  for (int s = kB; s < slices; s += kB) {
+#pragma unroll
+    for (int k = 0; k < kB; ++k) v[k] = pe[(int64_t)min(s + k, slices - 1) * n1];
+#pragma unroll
+    for (int k = 0; k < kB; ++k) m += s + k < slices ? v[k] : 0.f;
+  }
   __syncthreads();
-  const int rpb = 256 / r;
-  const int64_t i = (int64_t)blockIdx.x * rpb + tid / r;
-  const int q = tid % r;
-  const bool act = tid < rpb * r && i < N;
   float nv = 0.f;
   unsigned int mine = 0;
   if (act) {
     float den = 0.f;
-    for (int t = 0; t < r; ++t) den = fmaf(B[i * r + t], H[t * r + q], den);
+#pragma unroll
+    for (int t = 0; t < kR; ++t)
+      if (t < r) den = fmaf(row[t], H[t * r + q], den);
+    for (int t = kR; t < r; ++t) den = fmaf(br[t], H[t * r + q], den);
     double dd = (double)den;
     if (dd < eps) {
       dd = eps;
       mine = 1;
     }
-    nv = (float)(((double)B[i * r + q] * (double)M[i * r + q]) / dd);
+    nv = (float)(((double)old * (double)m) / dd);
   }
   if (mine) atomicAdd(&nclip, mine);
   __syncthreads();  // every row of the block is read before any is written
@@ -249,12 +336,12 @@ __global__ __launch_bounds__(256) void cp_mu_k(float *__restrict__ B, const floa
   if (tid == 0 && nclip) atomicAdd(clips, (unsigned long long)nclip);
 }
 
-nnc_status launch_cp_mu(float *B, const float *M, const float *S, int d, int n, int64_t N, int r,
+nnc_status launch_cp_mu(float *B, const float *part, int64_t slices, const float *S, int d, int n, int64_t N, int r,
                         double eps, unsigned long long *clips, hipStream_t s) {
   if (r < 1 || r > 32) return fail(NNC_EUNSUPPORTED, "rank %d outside [1, 32]", r);
   const int64_t rpb = 256 / r;
-  hipLaunchKernelGGL(cp_mu_k, dim3((unsigned)((N + rpb - 1) / rpb)), dim3(256), 0, s, B, M, S, d, n, N,
-                     r, eps, clips);
+  hipLaunchKernelGGL(cp_mu_k, dim3((unsigned)((N + rpb - 1) / rpb)), dim3(256), 0, s, B, part,
+                     (int)slices, S, d, n, N, r, eps, clips);
   NNC_HIP(hipGetLastError());
   return NNC_OK;
 }

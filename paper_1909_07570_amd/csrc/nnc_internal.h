@@ -274,10 +274,14 @@ nnc_status launch_small_with_core(const float *in, int64_t P, int64_t N, int64_t
                                   const CoreArgsHost &h, hipStream_t s);
 // out[e] = sum_{b < nparts} part[b][e] (fixed order)
 // Nonnegative CP of the data tensor (cpx_kernels.hip).
+// launch_diag: part <- the diag_slices(A, Nt, C) partial sums [Nt][r] of M, and in the same launch the
+// Gram gS = gB^T gB where gB is not null (diag_gram_fits(gN, r)); launch_cp_mu adds the slices.
 nnc_status launch_diag(const float *Y, int rho_first, int64_t A, int64_t Nt, int64_t C, const float *WA,
-                       const float *WC, int r, float *out, float *part, hipStream_t s);
+                       const float *WC, int r, float *part, const float *gB, int64_t gN, float *gS, hipStream_t s);
+int64_t diag_slices(int64_t A, int64_t Nt, int64_t C);
 int64_t diag_part_floats(int64_t A, int64_t Nt, int64_t C, int r);
-nnc_status launch_cp_mu(float *B, const float *M, const float *S, int d, int n, int64_t N, int r,
+bool diag_gram_fits(int64_t N, int r);
+nnc_status launch_cp_mu(float *B, const float *part, int64_t slices, const float *S, int d, int n, int64_t N, int r,
                         double eps, unsigned long long *clips, hipStream_t s);
 nnc_status launch_gram_block(const float *A, int64_t N, int r, float *S, hipStream_t s);
 // S[k] = A[k]^T A[k] for k < d in one launch (one workgroup per factor, R[k] <= 32).
