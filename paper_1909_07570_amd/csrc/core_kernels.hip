@@ -615,10 +615,10 @@ typedef float smf4 __attribute__((ext_vector_type(4)));
 // come from global memory (every block reads the same few kilobytes, held in L2) and are
 // loaded before the rows of `in`, so that the products of step s wait only for step s's
 // loads.
-template <int RM>
+template <int RM, int CW = 4>
 static __device__ void small_body(const SmallArgs &a, int64_t tile) {
   extern __shared__ __attribute__((aligned(16))) float sm[];
-  constexpr int RT = RM > 16 ? 2 : 1;
+  constexpr int RT = RM > 16 ? 2 : 1, TW = 16 * CW, RS = TW + 4;
   const float *__restrict__ in = a.in;
   const float *__restrict__ F = a.F;
   float *__restrict__ out = a.out;
@@ -629,18 +629,18 @@ static __device__ void small_body(const SmallArgs &a, int64_t tile) {
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool active = w < W;
   const int64_t PQ = P * Q;
-  const float *src[4];
+  const float *src[CW];
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {  // the lane's column of each 16-column group
-    const int64_t e = tile * 64 + 16 * c + li;
+  for (int c = 0; c < CW; ++c) {  // the lane's column of each 16-column group
+    const int64_t e = tile * TW + 16 * c + li;
     const int64_t ee = e < PQ ? e : 0;
     const int64_t p = ee / Q, q = ee - (ee / Q) * Q;
     src[c] = in + p * N * Q + q;
   }
   const int span = W * kSmallRows;  // rows of a round
-  smf4 acc[4][RT];
+  smf4 acc[CW][RT];
 #pragma unroll
-  for (int c = 0; c < 4; ++c)
+  for (int c = 0; c < CW; ++c)
 #pragma unroll
     for (int t = 0; t < RT; ++t) acc[c][t] = smf4{0.f, 0.f, 0.f, 0.f};
   // Addresses: one 64-bit product per pointer and round; step st adds 4 st rows, a
@@ -662,10 +662,10 @@ static __device__ void small_body(const SmallArgs &a, int64_t tile) {
       }
     }
     __builtin_amdgcn_sched_barrier(0);
-    float xv[kSteps][4];
-    const float *x0[4], *xl[4];
+    float xv[kSteps][CW];
+    const float *x0[CW], *xl[CW];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
+    for (int c = 0; c < CW; ++c) {
       x0[c] = src[c] + n0 * Q;
       xl[c] = src[c] + (N - 1) * Q;  // rows past N meet zero factor entries
     }
@@ -673,7 +673,7 @@ static __device__ void small_body(const SmallArgs &a, int64_t tile) {
     for (int st = 0; st < kSteps; ++st) {
       const bool inside = n0 + 4 * st < N;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) xv[st][c] = *(inside ? x0[c] + 4 * st * Q : xl[c]);
+      for (int c = 0; c < CW; ++c) xv[st][c] = *(inside ? x0[c] + 4 * st * Q : xl[c]);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -684,38 +684,38 @@ static __device__ void small_body(const SmallArgs &a, int64_t tile) {
         const int64_t n = nb + w * kSmallRows + 4 * st + lg;
         const float b = (n < N && 16 * t + li < R) ? fb[st][t] : 0.f;
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
+        for (int c = 0; c < CW; ++c)
           acc[c][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[st][c], b, acc[c][t], 0, 0, 0);
       }
     }
   }
-  float *red = sm;  // red[w][r][kRedStride], columns 0 .. 63 used
+  float *red = sm;  // red[w][r][RS], columns 0 .. TW - 1 used
   if (active) {
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
       const int r = 16 * t + li;
       if (r < RM) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c)  // columns 16 c + 4 lg .. + 3: one 16-byte write
-          *reinterpret_cast<smf4 *>(red + (w * RM + r) * kRedStride + 16 * c + 4 * lg) = acc[c][t];
+        for (int c = 0; c < CW; ++c)  // columns 16 c + 4 lg .. + 3: one 16-byte write
+          *reinterpret_cast<smf4 *>(red + (w * RM + r) * RS + 16 * c + 4 * lg) = acc[c][t];
       }
     }
   }
   __syncthreads();
-  for (int idx = tid; idx < RM * 64; idx += blockDim.x) {
-    const int r = idx >> 6, l = idx & 63;
-    const int64_t e2 = tile * 64 + l;
+  for (int idx = tid; idx < RM * TW; idx += blockDim.x) {
+    const int r = idx / TW, l = idx % TW;
+    const int64_t e2 = tile * TW + l;
     if (r >= R || e2 >= PQ) continue;
-    float s2 = red[r * kRedStride + l];
-    for (int ww = 1; ww < W; ++ww) s2 += red[(ww * RM + r) * kRedStride + l];
+    float s2 = red[r * RS + l];
+    for (int ww = 1; ww < W; ++ww) s2 += red[(ww * RM + r) * RS + l];
     const int64_t p2 = e2 / Q, q2 = e2 - (e2 / Q) * Q;
     out[(p2 * R + r) * Q + q2] = s2;
   }
 }
 
-template <int RM>
+template <int RM, int CW>
 __global__ __launch_bounds__(64 * kSmallMaxWaves) void ttm_small_k(SmallArgs a) {
-  small_body<RM>(a, blockIdx.x);
+  small_body<RM, CW>(a, blockIdx.x);
 }
 
 static bool small_args(const float *in, int64_t P, int64_t N, int64_t Q, const float *F,
@@ -747,9 +747,15 @@ nnc_status launch_ttm_small(const float *in, int64_t P, int64_t N, int64_t Q, co
   if (!small_args(in, P, N, Q, F, ldl, ldr, R, out, &a, &RM, &tiles))
     return fail(NNC_EUNSUPPORTED, "ttm_small: R %lld, N %lld or P*Q out of range", (long long)R,
                 (long long)N);
+  // Fewer 64-pair tiles than CUs: tiles of 16 pairs, four times the blocks and a quarter of the loads
+  // of each (the same sums): 8192 pairs, N 256, R 32 9.7 -> 6.2 us.  Above, 64 pairs a block already
+  // fill the chip (512 tiles: 7.2 us either way).
+  const bool narrow = tiles < device_cu_count();
   const size_t lds = small_lds(a.W, RM);
-  const dim3 g((unsigned)tiles), b(64 * a.W);
-#define NNC_SMALL(RMV) hipLaunchKernelGGL(ttm_small_k<RMV>, g, b, lds, s, a)
+  const dim3 g((unsigned)(narrow ? (P * Q + 15) / 16 : tiles)), b(64 * a.W);
+#define NNC_SMALL(RMV)                                                       \
+  if (narrow) hipLaunchKernelGGL((ttm_small_k<RMV, 1>), g, b, lds, s, a);    \
+  else hipLaunchKernelGGL((ttm_small_k<RMV, 4>), g, b, lds, s, a)
   switch (RM / 4) {
     case 1: NNC_SMALL(4); break;
     case 2: NNC_SMALL(8); break;
