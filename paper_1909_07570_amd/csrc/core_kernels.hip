@@ -711,14 +711,18 @@ nnc_status launch_ttm_small(const float *in, int64_t P, int64_t N, int64_t Q, co
   if (!small_args(in, P, N, Q, F, ldl, ldr, R, out, &a, &RM, &tiles))
     return fail(NNC_EUNSUPPORTED, "ttm_small: R %lld, N %lld or P*Q out of range", (long long)R,
                 (long long)N);
-  // Fewer 64-pair tiles than CUs: tiles of 16 pairs, four times the blocks and a quarter of the loads
-  // of each (the same sums): 8192 pairs, N 256, R 32 9.7 -> 6.2 us.  Above, 64 pairs a block already
-  // fill the chip (512 tiles: 7.2 us either way).
-  const bool narrow = tiles < device_cu_count();
+  // Narrower tiles are more blocks of fewer loads each (the same sums), as long as all waves are
+  // resident at once (16 a CU: what the registers and 1024-thread blocks leave).  8192 pairs, N 256,
+  // R 32: 9.7 us at 64 pairs a block, 6.2 at 16; 32768, N 128, R 16: 7.2, 6.4 at 32; 10240, N 512, R 20:
+  // 10.6 at 64, 13.6 at 16 (640 blocks of 16 waves).
+  const int64_t waves = (int64_t)device_cu_count() * 16;
+  int cw = 4;
+  while (cw > 1 && (P * Q + 8 * cw - 1) / (8 * cw) * a.W <= waves) cw /= 2;
   const size_t lds = small_lds(a.W, RM);
-  const dim3 g((unsigned)(narrow ? (P * Q + 15) / 16 : tiles)), b(64 * a.W);
+  const dim3 g((unsigned)((P * Q + 16 * cw - 1) / (16 * cw))), b(64 * a.W);
 #define NNC_SMALL(RMV)                                                       \
-  if (narrow) hipLaunchKernelGGL((ttm_small_k<RMV, 1>), g, b, lds, s, a);    \
+  if (cw == 1) hipLaunchKernelGGL((ttm_small_k<RMV, 1>), g, b, lds, s, a);   \
+  else if (cw == 2) hipLaunchKernelGGL((ttm_small_k<RMV, 2>), g, b, lds, s, a); \
   else hipLaunchKernelGGL((ttm_small_k<RMV, 4>), g, b, lds, s, a)
   switch (RM / 4) {
     case 1: NNC_SMALL(4); break;

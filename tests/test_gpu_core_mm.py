@@ -1,4 +1,4 @@
-"""Small contractions by 16 and 64 pairs a block, and core slices contracted on the matrix cores, at
+"""Small contractions by 16, 32 and 64 pairs a block, and core slices contracted on the matrix cores, at
 the edges of their tiles, against FP64 sweeps of the same start."""
 import numpy as np
 import pytest
@@ -20,8 +20,10 @@ SWEEPS = 2
         ((40, 33, 50), (16, 17, 15)),  # one and two tiles of ranks
         ((36, 45, 64), (24, 20, 9)),
         ((34, 32, 48), (32, 32, 16)),
-        ((510, 40, 34), (6, 5, 32)),  # 16320 pairs: 255 tiles of 64
-        ((513, 40, 34), (6, 5, 32)),  # 16416: 257
+        ((510, 100, 34), (6, 5, 32)),  # 16320 pairs, four waves a block: tiles of 16
+        ((513, 100, 34), (6, 5, 32)),  # 16416: tiles of 32
+        ((200, 500, 34), (6, 5, 32)),  # 6400, sixteen waves: tiles of 32
+        ((300, 500, 34), (6, 5, 32)),  # 9600: tiles of 64
         ((12, 10, 11, 9), (3, 4, 5, 6)),
         ((20, 18, 17, 19), (16, 15, 16, 13)),  # slices of several tiles a wave, one core row a block
         ((6, 7, 5, 6, 8), (2, 5, 3, 4, 3)),
