@@ -74,31 +74,34 @@ __device__ inline double rsqrt_d(double x) {
 // A wave's own LDS exchange: what its lanes wrote is there for its next reads.
 __device__ inline void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
+// x of lane k, in scalar registers: the exchanges below run without LDS, whose write, wait and
+// broadcast reads were half of a pivot's time.
+__device__ inline double lane_value(double x, int k) {
+  const long long v = __double_as_longlong(x);
+  const unsigned int lo = __builtin_amdgcn_readlane((int)v, k), hi = __builtin_amdgcn_readlane((int)(v >> 32), k);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
 // Inverse of the r x r matrix whose row i lane i holds in a (r <= RM), by Gauss-Jordan elimination
-// without pivoting, in place; every lane of one wave takes part.  row: RM doubles of LDS (16-byte
-// aligned) of this wave alone.  Returns the number of pivots that are not positive.
+// without pivoting, in place; every lane of one wave takes part.  Returns the number of pivots that
+// are not positive.
 template <int RM>
-__device__ inline unsigned int wave_inverse(double (&a)[RM], int r, int lane, double *row) {
+__device__ inline unsigned int wave_inverse(double (&a)[RM], int r, int lane) {
   unsigned int bad = 0;
 #pragma unroll
   for (int k = 0; k < RM; ++k)
     if (k < r) {
-      if (lane == k) {
-#pragma unroll
-        for (int j = 0; j < RM; j += 2) *reinterpret_cast<d2 *>(row + j) = d2{a[j], a[j + 1]};
-      }
-      wave_fence();
-      const double p = row[k], ip = rcp_d(p), f = a[k] * ip;
+      const double p = lane_value(a[k], k), ip = rcp_d(p);
       if (!(p > 0.0)) ++bad;
+      const bool own = lane == k;
+      const double f = own ? -ip : a[k] * ip;  // row k itself becomes row k / p
 #pragma unroll
-      for (int j = 0; j < RM; j += 2) {
-        const d2 v = *reinterpret_cast<const d2 *>(row + j);
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-          if (j + q != k) a[j + q] = lane == k ? v[q] * ip : fma(-f, v[q], a[j + q]);
-      }
-      a[k] = lane == k ? ip : -f;
-      wave_fence();  // the row is read before the next one overwrites it
+      for (int j = 0; j < RM; ++j)
+        if (j != k) {
+          const double v = lane_value(a[j], k);
+          a[j] = fma(-f, v, own ? 0.0 : a[j]);
+        }
+      a[k] = -f;
     }
   return bad;
 }
@@ -107,7 +110,7 @@ __device__ inline unsigned int wave_inverse(double (&a)[RM], int r, int lane, do
 // diagonal) and the inverse of L into Li, by one wave; lane i owns row i of L, then column i of Li.
 // Returns the number of diagonal entries that are not positive.
 template <int RM>
-__device__ inline unsigned int wave_cholesky(const double *W, double *L, double *Li, int r, int lane, double *col) {
+__device__ inline unsigned int wave_cholesky(const double *W, double *L, double *Li, int r, int lane) {
   unsigned int bad = 0;
   const int i0 = lane < r ? lane : 0;
   double a[RM], inv[RM];
@@ -117,17 +120,14 @@ __device__ inline unsigned int wave_cholesky(const double *W, double *L, double 
   for (int j = 0; j < RM; ++j) {
     inv[j] = 0.0;
     if (j < r) {
-      if (lane < RM) col[lane] = a[j];
-      wave_fence();
-      const double d = col[j];
+      const double d = lane_value(a[j], j);
       if (!(d > 0.0)) ++bad;
       inv[j] = rsqrt_d(d);
       const double l = lane >= j ? a[j] * inv[j] : 0.0, li = l * inv[j];
 #pragma unroll
       for (int k = 0; k < RM; ++k)
-        if (k > j) a[k] = fma(-li, col[k], a[k]);  // col[k] = L[k][j] / inv[j]
+        if (k > j) a[k] = fma(-li, lane_value(a[j], k), a[k]);  // lane k: L[k][j] / inv[j]
       a[j] = l;
-      wave_fence();
     }
   }
   if (lane < r) {
@@ -184,8 +184,8 @@ __global__ __launch_bounds__(kLsThreads) void ls_small_k(const float *__restrict
   __shared__ unsigned int bad;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   constexpr int P = RM * RM, H = RM / 2;
-  double *Z = sd, *Kinv = sd + P, *W = sd + 2 * P, *L = sd + 3 * P, *Li = sd + 4 * P, *M = sd + 5 * P, *line = sd + 6 * P;
-  double *rows = line + RM;  // kLsChunk x RM, zeros past R; then the ranges' sums of Z
+  double *Z = sd, *Kinv = sd + P, *W = sd + 2 * P, *L = sd + 3 * P, *Li = sd + 4 * P, *M = sd + 5 * P;
+  double *rows = sd + 6 * P;  // kLsChunk x RM, zeros past R; then the ranges' sums of Z
   if (tid == 0) bad = 0;
   for (int e = tid; e < 6 * P; e += kLsThreads) sd[e] = 0.0;
   // Z = num^T num by blocks of 2 x 2 entries times row ranges, waves 1 and up; K^{-1} by wave 0
@@ -225,7 +225,7 @@ __global__ __launch_bounds__(kLsThreads) void ls_small_k(const float *__restrict
 #pragma unroll
       for (int j = 0; j < RM; ++j) a[j] = lane < R && j < R ? (K ? (double)K[lane * R + j] : (lane == j ? 1.0 : 0.0)) : 0.0;
       unsigned int nbad = 0;
-      if (K) nbad = wave_inverse<RM>(a, R, lane, line);
+      if (K) nbad = wave_inverse<RM>(a, R, lane);
       if (lane < R) {
 #pragma unroll
         for (int j = 0; j < RM; ++j) Kinv[lane * RM + j] = a[j];
@@ -248,7 +248,7 @@ __global__ __launch_bounds__(kLsThreads) void ls_small_k(const float *__restrict
   small_mm<RM>(Z, false, Kinv, false, M, R);  // Z K^{-1}
   small_mm<RM>(Kinv, false, M, false, W, R);  // K^{-1} Z K^{-1} = A*^T A*
   if (wave == 0) {
-    const unsigned int nbad = wave_cholesky<RM>(W, L, Li, R, lane, line);
+    const unsigned int nbad = wave_cholesky<RM>(W, L, Li, R, lane);
     if (lane == 0 && nbad) atomicAdd(&bad, nbad);
   }
   __syncthreads();
@@ -333,7 +333,6 @@ struct LsInvArgs {
 // Sinv[k] = S[k]^{-1} (as floats), one wave per mode.
 template <int RM>
 __global__ __launch_bounds__(64) void ls_inv_k(LsInvArgs g, unsigned long long *fails) {
-  __shared__ __attribute__((aligned(16))) double line[RM];
   const float *S = g.S[0];
   float *Sinv = g.Sinv[0];
   int R = g.R[0];
@@ -348,7 +347,7 @@ __global__ __launch_bounds__(64) void ls_inv_k(LsInvArgs g, unsigned long long *
   double a[RM];
 #pragma unroll
   for (int j = 0; j < RM; ++j) a[j] = lane < R && j < R ? (double)S[lane * R + j] : 0.0;
-  const unsigned int bad = wave_inverse<RM>(a, R, lane, line);
+  const unsigned int bad = wave_inverse<RM>(a, R, lane);
   if (lane < R) {
 #pragma unroll
     for (int j = 0; j < RM; ++j)
@@ -361,10 +360,10 @@ __global__ __launch_bounds__(64) void ls_inv_k(LsInvArgs g, unsigned long long *
 
 static int ls_bound(int64_t R) { return R <= 8 ? 8 : (int)((R + 3) / 4 * 4); }
 
-// LDS of ls_small_k: six R x R matrices, one line, and a chunk of rows or the ranges' sums of Z.
+// LDS of ls_small_k: six R x R matrices and a chunk of rows or the ranges' sums of Z.
 static size_t ls_small_lds(int RM) {
   const int split = std::min(kLsSplit, (kLsThreads - 64) / (RM / 2 * (RM / 2)));
-  return sizeof(double) * (size_t)(6 * RM * RM + RM + std::max(kLsChunk * RM, split * RM * RM));
+  return sizeof(double) * (size_t)(6 * RM * RM + std::max(kLsChunk * RM, split * RM * RM));
 }
 
 nnc_status launch_ls_factor(const float *num, const float *K, int64_t N, int64_t R, float *A, double *T, float *Lf,
