@@ -507,7 +507,7 @@ __global__ __launch_bounds__(64 * kMidWaves) __attribute__((amdgpu_waves_per_eu(
   auto load = [&](u4 (&vv)[8], int s) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      const int n = min(32 * s + 8 * lg + j, nlim);
+      const int n = min(32 * s + (RAG ? 4 * j + lg : 8 * lg + j), nlim);
       vv[j] = p_load_nt<false, RAG>(xp + (int64_t)n * Q);
     }
   };
@@ -551,7 +551,8 @@ __global__ __launch_bounds__(64 * kMidWaves) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const f4 xv = __builtin_bit_cast(f4, vv[j]);
-        const float *brow = fl + (32 * s + 8 * lg + j) * RS + li;
+        // RAG: rows in order, as in the last-mode kernel (the general kernel's sum)
+        const float *brow = fl + (32 * s + (RAG ? 4 * j + lg : 8 * lg + j)) * RS + li;
 #pragma unroll
         for (int nt = 0; nt < RT; ++nt) {
           const float b = brow[nt * 16];
@@ -705,9 +706,22 @@ __global__ __launch_bounds__(kLdsThreads) __attribute__((amdgpu_waves_per_eu(CPR
 #pragma unroll
       for (int nt = 0; nt < RT; ++nt) acc[nt] = f4{0.f, 0.f, 0.f, 0.f};
     }
+    if (RAG && !BF) {
+      // Rows of four k in order: a step's products are added one after the other, so an output is
+      // one chain of multiply-adds in the order of k, the general kernel's sum bit for bit (small
+      // cores' CP fits amplify another order).  Scalar reads; these passes wait for X.
+      const float *xr = reinterpret_cast<const float *>(stg + li * SS) + lg;
+#pragma unroll
+      for (int st = 0; st < KC / 4; ++st) {
+        const float x = xr[4 * st];
+#pragma unroll
+        for (int nt = 0; nt < RT; ++nt)
+          acc[nt] = p_mfma_f32(x, fl[min(nt * 16 + li, FR - 1) * KS + h * KC + 4 * st + lg], acc[nt]);
+      }
+    }
     const unsigned char *srow = stg + li * SS + lg * 16;
 #pragma unroll
-    for (int st = 0; st < CPR / 4; ++st) {
+    for (int st = 0; st < (RAG && !BF ? 0 : CPR / 4); ++st) {
       const u4 a = *reinterpret_cast<const u4 *>(srow + st * 64);
       const int kk = h * KC + st * KSTEP;
       if (BF) {
