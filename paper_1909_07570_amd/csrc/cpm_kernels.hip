@@ -28,12 +28,10 @@
 // each is what the matrix cores need); the rest is twelve phases of 0.7 to 2.3 thousand, chains of
 // a few LDS round trips and, in the updates, an FP64 division.  Sixteen waves were slower: every
 // instruction of a phase then issues four times per SIMD.
-#include <string.h>
-
-#include <algorithm>
 #include <map>
 #include <mutex>
 
+#include "cpm_plan.h"
 #include "nnc_internal.h"
 
 namespace nnc {
@@ -44,61 +42,8 @@ struct CpmPtrs {
   float *p[kMaxDim];
 };
 
-constexpr int kCpmWaves = 8;  // two per SIMD, 256 registers each
-
-// One of the two products: `tiles` 16-row tiles times `split` ranges of `kper` steps (a step is
-// four values of the contracted index) are units, unit u = tile + tiles * range; wave w takes
-// units w, w + waves, ..., NS at a time (NS > 1 only without ranges: those tiles share their
-// operand rows), in `passes` passes.
-struct CpmProd {
-  int tiles, split, kper, passes;
-};
-
-struct CpmArgs {
-  int d, s;
-  int dims[5];
-  int size, pL, pR, sumdim, maxdim;  // sumdim: modes rounded up to 4 rows
-  CpmProd v, u;
-};
-
 static __device__ inline f4 cpm_mfma(float a, float b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-// Rows of every array over ranks hold RS = 8, 16 or 32 values, zeros past the rank.  LDS floats of
-// a fit with `threads` threads:
-//   factors, two buffers | Grams (d RS WS) | H (RS WS) | partial sums of M_n (or, with one mode
-//   in a group, none) | KR of the left group | KR of the right group (groups of one mode are the
-//   factor itself) | V or U, by ranges of the contracted index.  The residual's FP64 sums reuse
-//   V and U, which are at least 4 floats a thread.
-// Rows of the Grams and of H are WS = RS + 4 floats apart: an update reads 16 of them at once, 16
-// bytes each, from 64 different banks.  All of it starts as zeros: operand reads past an array's
-// last row meet zeros of T, and have to be finite.
-static int64_t cpm_lds_floats(const CpmArgs &a, int RS, int threads) {
-  int64_t n = 2 * a.sumdim * RS + (int64_t)(a.d + 1) * RS * (RS + 4);
-  n += std::max<int64_t>(4 * (int64_t)threads, (int64_t)a.maxdim * RS);
-  if (a.s > 1) n += a.pL * RS;
-  if (a.d - a.s > 1) n += a.pR * RS;
-  n += std::max<int64_t>(std::max<int64_t>((int64_t)a.v.split * a.pL, (int64_t)a.u.split * a.pR) * RS, 4 * (int64_t)threads);
-  return n + 128 * RS;  // products of one pass read up to 32 step groups of rows
-}
-
-// The unit of one wave at slot s of a pass: tile t, range q (q >= split: none).
-struct CpmUnit {
-  int t, q;
-};
-template <int NS>
-static __device__ inline CpmUnit cpm_unit(const CpmProd &p, int wave, int nw, int pass, int s) {
-  CpmUnit u{wave + nw * (NS * pass + s), 0};
-  if (NS == 1) {
-    while (u.t >= p.tiles) {
-      u.t -= p.tiles;
-      ++u.q;
-    }
-  } else if (u.t >= p.tiles) {
-    u.q = p.split;
-  }
-  return u;
 }
 
 // Fragment of T (TR: of T^t) for a unit: `step` of its range stands for four contracted indices,
@@ -604,61 +549,8 @@ __global__ __launch_bounds__(64 * kCpmWaves) void nncp_mm_k(const float *__restr
 }
 
 // ------------------------------------------------------------------ launch
-constexpr int64_t kCpmLds = 158 * 1024;
-
-static int cpm_rs(int r) { return r <= 8 ? 8 : (r <= 16 ? 16 : 32); }
-
-static CpmProd cpm_prod(int rows, int ks, int nw, int ns) {
-  CpmProd p;
-  p.tiles = (rows + 15) / 16;
-  const int steps = (ks + 3) / 4;
-  p.split = ns > 1 ? 1 : std::max(1, std::min(nw / p.tiles, steps));
-  p.kper = (steps + p.split - 1) / p.split;
-  p.split = (steps + p.kper - 1) / p.kper;
-  p.passes = (p.tiles * p.split + nw * ns - 1) / (nw * ns);
-  return p;
-}
-
-// Values of T that a lane holds for a product.
-static int cpm_regs(const CpmProd &p, int ns) { return p.passes * ((p.kper + 3) / 4) * 4 * ns; }
-
-// Tiles of T a wave takes at a time: several share their operand rows once every wave has some.
-static int cpm_slots(const CpProblem &pb, int threads) {
-  int64_t pl = 1;
-  for (int k = 0; k < (pb.d + 1) / 2; ++k) pl *= pb.dims[k];
-  const int64_t per = ((pl + 15) / 16 + threads / 64 - 1) / (threads / 64);
-  return per > 4 ? 8 : (per > 1 ? 4 : 1);
-}
-
-static CpmArgs cpm_args(const CpProblem &pb, int threads) {
-  CpmArgs a;
-  memset(&a, 0, sizeof a);
-  a.d = pb.d;
-  a.s = (pb.d + 1) / 2;
-  a.size = (int)pb.size;
-  a.pL = a.pR = 1;
-  for (int k = 0; k < a.d; ++k) {
-    a.dims[k] = (int)pb.dims[k];
-    (k < a.s ? a.pL : a.pR) *= a.dims[k];
-    a.sumdim += (a.dims[k] + 3) & ~3;
-    a.maxdim = std::max(a.maxdim, a.dims[k]);
-  }
-  a.v = cpm_prod(a.pL, a.pR, threads / 64, cpm_slots(pb, threads));
-  a.u = cpm_prod(a.pR, a.pL, threads / 64, 1);
-  return a;
-}
-
-// Cores of fewer than 512 entries stay with nncp_k: there is little to gain there (4.6 us a sweep
-// of 3 x 4 x 5 at rank 5 against 3.1 here), and such small fits carry every change of rounding far
-// (an order of sums of its own moved single factors 2e-6, as far as either lies from 64 bits).
-// Orders 3 to 5 with modes of at most 64 (one wave forms a Gram, one pass of the block an
-// update) whose working set fits one CU; other shapes stay with nncp_k.
 bool nncp_mm_fits(const CpProblem &pb, int max_rank, int threads) {
-  if (pb.d < 3 || pb.d > 5 || pb.size < 512 || pb.size > (1 << 17) || max_rank > 32) return false;
-  for (int k = 0; k < pb.d; ++k)
-    if (pb.dims[k] > 64) return false;
-  threads = std::min(threads, 64 * kCpmWaves);
-  return cpm_lds_floats(cpm_args(pb, threads), cpm_rs(max_rank), threads) * 4 <= kCpmLds;
+  return cpm_fits(pb.d, pb.dims, pb.size, max_rank, threads);
 }
 
 static nnc_status cpm_allow_lds(const void *kern, int64_t bytes) {
@@ -676,17 +568,14 @@ static nnc_status cpm_allow_lds(const void *kern, int64_t bytes) {
 nnc_status launch_nncp_mm(const float *T, const CpProblem &pb, int nbatch, const int *d_ranks, int max_rank,
                           float *const *d_factor_ptrs, float *const *single_ptrs, int iters, double eps,
                           double *d_resid, unsigned long long *clips, int threads, hipStream_t s) {
-  threads = std::min(threads, 64 * kCpmWaves);
-  CpmArgs a = cpm_args(pb, threads);
-  const int64_t lds = cpm_lds_floats(a, cpm_rs(max_rank), threads) * 4;
+  threads = std::min(threads, kCpmMaxThreads);
   if (!nncp_mm_fits(pb, max_rank, threads)) return fail(NNC_EUNSUPPORTED, "nnCP shape does not suit the matrix-core kernel");
+  const CpmPlan pl = cpm_plan(pb.d, pb.dims, threads);
+  const CpmArgs &a = pl.a;
+  if (pl.ns > 1 && a.v.split > 1) return fail(NNC_EUNSUPPORTED, "nnCP: ranges with several slots");
+  const int64_t lds = cpm_lds_floats(a, cpm_rs(max_rank), threads) * 4;
   CpmPtrs p0;
   for (int k = 0; k < kMaxDim; ++k) p0.p[k] = (single_ptrs && k < pb.d) ? single_ptrs[k] : nullptr;
-  // T in registers when each product takes one pass and a lane's share fits 32 or 64 values per
-  // layout, else from the L2 each sweep
-  const int ns = cpm_slots(pb, threads), g = std::max(cpm_regs(a.v, ns), cpm_regs(a.u, 1));
-  const int nr = g > 64 || a.v.passes > 1 || a.u.passes > 1 ? 0 : (g > 32 ? 64 : 32);
-  if (!nr) a.v.passes = (a.v.tiles * a.v.split + 4 * (threads / 64) - 1) / (4 * (threads / 64));  // four slots there
 #define NNC_CPM5(RSV, NSV, NRV, DV)                                                                                \
   do {                                                                                                             \
     NNC_TRY(cpm_allow_lds(reinterpret_cast<const void *>(nncp_mm_k<RSV, NSV, NRV, DV>), lds));                     \
@@ -704,23 +593,21 @@ nnc_status launch_nncp_mm(const float *T, const CpProblem &pb, int nbatch, const
   } while (0)
 #define NNC_CPM3(RSV, NSV)     \
   do {                         \
-    if (nr == 32)              \
+    if (pl.nr == 32)           \
       NNC_CPM4(RSV, NSV, 32);  \
-    else if (nr == 64)         \
+    else if (pl.nr == 64)      \
       NNC_CPM4(RSV, NSV, 64);  \
     else                       \
       NNC_CPM4(RSV, NSV, 0);   \
   } while (0)
-#define NNC_CPM(RSV)                          \
-  do {                                        \
-    if (ns == 8 && nr)                        \
-      NNC_CPM4(RSV, 8, 64);                   \
-    else if (ns == 1 && nr == 32)             \
-      NNC_CPM4(RSV, 1, 32);                   \
-    else if (ns == 1 && nr == 64)             \
-      NNC_CPM4(RSV, 1, 64);                   \
-    else                                      \
-      NNC_CPM3(RSV, 4);                       \
+#define NNC_CPM(RSV)          \
+  do {                        \
+    if (pl.ns == 8)           \
+      NNC_CPM4(RSV, 8, 64);   \
+    else if (pl.ns == 4)      \
+      NNC_CPM3(RSV, 4);       \
+    else                      \
+      NNC_CPM3(RSV, 1);       \
   } while (0)
   if (max_rank <= 8)
     NNC_CPM(8);
