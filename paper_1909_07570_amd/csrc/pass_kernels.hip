@@ -11,6 +11,7 @@
 // zero-padded to 16-column tiles) lives in LDS.
 #include <map>
 #include <mutex>
+#include <type_traits>
 
 #include "nnc_internal.h"
 
@@ -83,18 +84,46 @@ static __device__ inline u4 p_shift_down(u4 v, int bits) {
 constexpr int kPassThreads = 256;
 constexpr int kUnitChunks = 16;  // 16-byte loads per lane per work unit
 
+// Output entries of the ragged kernels that come out as NaN are formed again one product after the
+// other, as the general kernel does: a matrix product also multiplies zeros (the factor's parts of a
+// value that bf16 holds, its rows past the contracted index, against values of X read in the place of
+// those past it), and zero times an infinity of X is NaN where the sum itself is infinite.  x and f: the
+// entry's first terms, xs and fs elements apart; a sum that is NaN stays so.
+static __device__ inline float p_value(const float *x) { return *x; }
+static __device__ inline float p_value(const uint16_t *x) { return p_bf2f(*x); }
+template <typename XT>
+static __device__ inline float p_chain(const XT *x, int64_t xs, const float *f, int64_t fs, int n) {
+  float acc = 0.f;
+#pragma unroll 1
+  for (int l = 0; l < n && acc == acc; ++l) acc = fmaf(f[l * fs], p_value(x + l * xs), acc);
+  return acc;
+}
+static __device__ inline bool p_any_nan(f4 v) {
+  return __builtin_expect(v[0] != v[0] || v[1] != v[1] || v[2] != v[2] || v[3] != v[3], 0);
+}
+
 // Columns q .. q + 3 of an output row in the ragged earlier-mode kernels.  A loader lane's chunk
 // is EPC columns of X from q8 = q rounded down to its chunk.  Where that chunk reaches past the
 // row's end it was read (and its columns computed) from the row's last whole 16 bytes, so `val`
 // then stands for columns qt .. qt + 3 with qt = Q - EPC + (q - q8), and only those from q8 on
-// are stored: the ones before belong to the chunk before.
-static __device__ inline void p_store_ragged(float *row, int64_t q, int64_t q8, int EPC, int64_t Q, f4 val, int acc) {
-  if (q8 + EPC <= Q) {
+// are stored: the ones before belong to the chunk before.  x: the contraction's first row of X, whose
+// n rows are Q apart; f: the output row's first factor entry.
+template <typename XT>
+static __device__ inline void p_store_ragged(float *row, int64_t q, int64_t q8, int EPC, int64_t Q, f4 val, int acc,
+                                             const XT *x, const float *f, int64_t ldl, int n) {
+  if (q8 >= Q) return;
+  const bool whole = q8 + EPC <= Q;
+  const int64_t qt = whole ? q : Q - EPC + (q - q8);
+  if (p_any_nan(val)) {
+#pragma unroll 1
+    for (int c = 0; c < 4; ++c)
+      if (val[c] != val[c]) val[c] = p_chain(x + qt + c, Q, f, ldl, n);
+  }
+  if (whole) {
     f4_el *o = reinterpret_cast<f4_el *>(row + q);
     if (acc) val += *o;  // a later chunk of the contracted index
     *o = val;
-  } else if (q8 < Q) {
-    const int64_t qt = Q - EPC + (q - q8);
+  } else {
 #pragma unroll
     for (int c = 0; c < 4; ++c)
       if (qt + c >= q8) row[qt + c] = acc ? row[qt + c] + val[c] : val[c];
@@ -406,7 +435,7 @@ __global__ __launch_bounds__(64 * kMidWaves) __attribute__((amdgpu_waves_per_eu(
         const int qq = (lane & 31) * 4;
         if (RAG && r < R) {
           const f4 val = *reinterpret_cast<const f4 *>(stg + r * 128 + qq);
-          p_store_ragged(out + (p * R + r) * Q, q0 + qq, q0 + (qq & ~7), 8, Q, val, acc_out);
+          p_store_ragged(out + (p * R + r) * Q, q0 + qq, q0 + (qq & ~7), 8, Q, val, acc_out, X + p * ldp, F + r * ldr, ldl, N);
         } else if (r < R && q0 + qq < Q) {
           f4 *o = reinterpret_cast<f4 *>(out + (p * R + r) * Q + q0 + qq);
           f4 val = *reinterpret_cast<const f4 *>(stg + r * 128 + qq);
@@ -447,7 +476,7 @@ __global__ __launch_bounds__(64 * kMidWaves) __attribute__((amdgpu_waves_per_eu(
           const int64_t qc = q0 + 64 * h + qq;
           if (RAG && r < R) {
             const f4 val = *reinterpret_cast<const f4 *>(stg + r * 64 + qq);
-            p_store_ragged(out + (p * R + r) * Q, qc, qc - (qq & 7), 8, Q, val, acc_out);
+            p_store_ragged(out + (p * R + r) * Q, qc, qc - (qq & 7), 8, Q, val, acc_out, X + p * ldp, F + r * ldr, ldl, N);
           } else if (r < R && qc < Q) {
             f4 *o = reinterpret_cast<f4 *>(out + (p * R + r) * Q + qc);
             f4 val = *reinterpret_cast<const f4 *>(stg + r * 64 + qq);
@@ -595,7 +624,7 @@ __global__ __launch_bounds__(64 * kMidWaves) __attribute__((amdgpu_waves_per_eu(
       const int qq = (lane & 15) * 4;
       if (RAG && r < R) {
         const f4 val = *reinterpret_cast<const f4 *>(stg + r * 64 + qq);
-        p_store_ragged(out + (p * R + r) * Q, q0 + qq, q0 + qq, 4, Q, val, acc_out);
+        p_store_ragged(out + (p * R + r) * Q, q0 + qq, q0 + qq, 4, Q, val, acc_out, X + p * ldp, F + r * ldr, ldl, N);
       } else if (r < R && q0 + qq < Q) {
         f4 *o = reinterpret_cast<f4 *>(out + (p * R + r) * Q + q0 + qq);
         f4 val = *reinterpret_cast<const f4 *>(stg + r * 64 + qq);
@@ -758,11 +787,19 @@ __global__ __launch_bounds__(kLdsThreads) __attribute__((amdgpu_waves_per_eu(CPR
       const int64_t rows = (M - t * 16) < 16 ? (M - t * 16) : 16;
       const int nfl = (int)rows * R;
       float *dst = out + t * 16 * (int64_t)R;
+      using XT = typename std::conditional<BF, uint16_t, float>::type;
+      auto term = [&](int e, float v) {  // entry e of the block: formed again where it is NaN
+        return v == v ? v : p_chain(static_cast<const XT *>(Xv) + (t * 16 + e / R) * ldx, 1, F + (e % R) * ldr, ldl, K);
+      };
 #pragma unroll
       for (int e0 = 0; e0 < 16 * RP; e0 += 256) {
         const int e = e0 + 4 * lane;
         if (RAG && e + 4 <= nfl) {  // the output may start at any element
           f4 val = *reinterpret_cast<const f4 *>(ot + e);
+          if (p_any_nan(val)) {
+#pragma unroll 1
+            for (int c = 0; c < 4; ++c) val[c] = term(e + c, val[c]);
+          }
           if (acc_out) val += *reinterpret_cast<const f4_el *>(dst + e);
           *reinterpret_cast<f4_el *>(dst + e) = val;
         } else if (e + 4 <= nfl) {
@@ -774,7 +811,10 @@ __global__ __launch_bounds__(kLdsThreads) __attribute__((amdgpu_waves_per_eu(CPR
             __builtin_nontemporal_store(val, reinterpret_cast<f4 *>(dst + e));
           }
         } else if (e < nfl) {
-          for (int q = e; q < nfl; ++q) dst[q] = acc_out ? dst[q] + ot[q] : ot[q];
+          for (int q = e; q < nfl; ++q) {
+            const float v = RAG ? term(q, ot[q]) : ot[q];
+            dst[q] = acc_out ? dst[q] + v : v;
+          }
         }
       }
     }
