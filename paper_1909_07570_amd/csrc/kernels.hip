@@ -5,7 +5,8 @@
 //   X viewed as [P][N][Q] (N = the contracted mode, Q = product of the later modes):
 //     out[p][r][q] = sum_n F(n, r) * X[p][n][q].
 // The matrix-core X-streaming kernels (pass_kernels.hip) take every shape with rank <= 32 and
-// rows of at least one 16-byte chunk; the general kernel here takes the rest.
+// rows of at least one 16-byte chunk, but for short contracted indices in rows that are not whole
+// chunks; the general kernel here takes the rest.
 #include <stdarg.h>
 #include <stdio.h>
 
@@ -92,8 +93,8 @@ nnc_status launch_ttm(const void *X, nnc_dtype xdt, int64_t P, int64_t N, int64_
     const nnc_status st = launch_pass(X, xdt, P, N, Q, F, ldl, ldr, R, out, s, kernel_name, reserve_cus);
     if (st != NNC_EUNSUPPORTED) return st;
   }
-  // every other shape (rank above 32, rows shorter than 16 bytes): one thread per
-  // (p, 4 columns r, q)
+  // every other shape (rank above 32, rows shorter than 16 bytes, short ragged ones): one thread
+  // per (p, 4 columns r, q)
   {
     const int64_t work = P * ((R + 3) / 4) * Q;
     const int grid = grid_for(work, 256, 65536);

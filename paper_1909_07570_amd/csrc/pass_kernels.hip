@@ -1025,6 +1025,28 @@ static nnc_status launch_last_lds(const void *X, bool bf, int64_t M, int64_t K, 
   return NNC_OK;
 }
 
+// Ragged rows that the general kernel takes sooner: short contracted indices, where a tile of 64 or 128
+// columns (16 rows in the last mode) of mostly padding costs more than a thread per output.  Both
+// times by what bounds them, in ns: a launch, then for the general kernel one thread's chain of loads
+// or all threads' work, for the ragged ones the factor's staging and the tiles.  Fitted to 2582 shapes
+// (N 1 .. 1000, rows of 5 .. 129, up to 2^25 entries; within 20 % of most); the general kernel is
+// taken unless 1.3 times slower, so that no shape there lost more than 7 % to it: 100000 x 2 x 9 FP32
+// at rank 1 6 us (ragged 100), 20000 x 20 x 5 at 5 9 (27), 301 x 250 x 9 at 20 stays ragged, 24 (87).
+// Below 128 rows of the last mode both are a launch's latency (4 and 6 us).
+static bool general_is_sooner(bool bf, int64_t P, int64_t N, int64_t Q, int64_t R) {
+  if (Q == 1 && (P < 128 || N >= 32)) return false;
+  const double threads = (double)P * ((R + 3) / 4) * Q, steps = (double)((N + 31) / 32);
+  const double general = 2900 + std::max(N * (R < 4 ? 200.0 : 360.0), threads * (2.2e-3 + N * (R < 4 ? 1.1e-3 : 2.4e-3)));
+  double ragged;
+  if (Q == 1)
+    ragged = 3900 + 30.0 * R + 1000 * steps + (double)((P + 15) / 16) * (0.3 + 0.1 * steps) * (R > 16 ? 2 : 1);
+  else if (bf)
+    ragged = 5400 + 150.0 * R + 1000 * steps + (double)(P * ((Q + 127) / 128)) * (0.95 + 0.35 * steps) * (R > 16 ? 2 : 1);
+  else
+    ragged = 3800 + 150.0 * R + 1000 * steps + (double)(P * ((Q + 63) / 64)) * (0.4 + 0.6 * steps) * (R > 16 ? 2 : 1);
+  return general < 1.3 * ragged;
+}
+
 // Returns NNC_EUNSUPPORTED (without recording an error) when the shape does not suit the
 // pipelined kernels, so the caller can fall back.  A contracted index too long for the
 // factor to fit in LDS is split into chunks, each a launch on its slab of X (with X's own
@@ -1040,6 +1062,7 @@ nnc_status launch_pass(const void *X, nnc_dtype xdt, int64_t P, int64_t N, int64
                    (Q == 1 ? N : Q) % (bf ? 8 : 4);
   if ((reinterpret_cast<uintptr_t>(X) & (bf ? 1u : 3u)) || (reinterpret_cast<uintptr_t>(out) & 3u))
     return NNC_EUNSUPPORTED;
+  if (rag && general_is_sooner(bf, P, N, Q, R)) return NNC_EUNSUPPORTED;
   const int esz = bf ? 2 : 4;
   const int RT = R <= 16 ? 1 : 2;
   const int waves = kPassThreads / 64;
