@@ -129,12 +129,34 @@ inline int64_t cpm_lds_floats(const CpmArgs &a, int RS, int threads) {
 // (an order of sums of its own moved single factors 2e-6, as far as either lies from 64 bits).
 // Orders 3 to 5 with modes of at most 64 (one wave forms a Gram, one pass of the block an
 // update) whose working set fits one CU; other shapes stay with nncp_k.
-inline bool cpm_fits(int d, const int64_t *dims, int64_t size, int max_rank, int threads) {
+inline bool cpm_takes(int d, const int64_t *dims, int64_t size, int max_rank, int threads) {
   if (d < 3 || d > 5 || size < 512 || size > (1 << 17) || max_rank > 32) return false;
   for (int k = 0; k < d; ++k)
     if (dims[k] > 64) return false;
   threads = std::min(threads, kCpmMaxThreads);
   return cpm_lds_floats(cpm_plan(d, dims, threads).a, cpm_rs(max_rank), threads) * 4 <= kCpmLds;
+}
+
+// Of those, the shapes that nncp_k is sooner with (us a sweep, here and there; 1710 fits of 3 to 5 modes):
+//   - 3-way tensors read from the L2 here at ranks up to 10, whose products fill at most 10 of 16 columns:
+//     nncp_k has one contraction to do for them too (40 x 40 x 40 at rank 3 43 and 19, 33 x 33 x 33 at
+//     8 36 and 19; 21 x 38 x 61 at 16 27 and 32);
+//   - small 3-way tensors at ranks 17 .. 22, held as 32 here (9 x 8 x 8 at 17 7.8 and 6.6, 7 x 13 x 13 at
+//     18 8.4 and 8.0; over 1400 entries 3 % sooner here and more);
+//   - 4-way tensors of a few rows and a long right group, whose two modes share the work of a rank here,
+//     while nncp_k holds the tensor in its LDS (2 x 1 x 51 x 39 at rank 8 33 and 18, 7 x 2 x 53 x 38 at 3
+//     34 and 25; 4 x 8 x 12 x 16 at 10 9.2 and 24).  The line is a fit: no shape beyond it lost more than
+//     a quarter, one before it is 14 % slower.
+inline bool cpm_later(const CpmPlan &pl, int max_rank) {
+  const CpmArgs &a = pl.a;
+  if (a.d == 3) return (!pl.nr && max_rank <= 10) || (max_rank > 16 && max_rank <= 22 && a.size <= 1400);
+  const int64_t quads = (max_rank + 3) / 4 * 4;
+  return a.d == 4 && !pl.nr && pl.ns == 1 && a.size <= 36000 && (int64_t)a.pR * a.pR > 6400 * a.pL * quads;
+}
+
+inline bool cpm_fits(int d, const int64_t *dims, int64_t size, int max_rank, int threads) {
+  return cpm_takes(d, dims, size, max_rank, threads) &&
+         !cpm_later(cpm_plan(d, dims, std::min(threads, kCpmMaxThreads)), max_rank);
 }
 
 }  // namespace nnc

@@ -2,7 +2,9 @@
 // shape and thread count that it takes, and counts how often each unit (16-row tile and range of the
 // contracted index) of the two products comes up: exactly once, within the registers of the variant.
 // Prints the number of plans and the first shapes that fail; the exit status is 1 if any does.
+// With arguments (rank, threads, modes): whether the kernel is the one that such a fit goes to.
 #include <cstdio>
+#include <cstdlib>
 #include <set>
 #include <vector>
 
@@ -39,7 +41,13 @@ static bool plan_ok(int d, const int64_t *dims, int threads) {
   return v && once<1>(a.u, a.pL, nw, pl.nr);
 }
 
-int main() {
+int main(int argc, char **argv) {
+  if (argc > 3) {
+    int64_t dims[8], size = 1;
+    for (int k = 3; k < argc; ++k) size *= dims[k - 3] = atoi(argv[k]);
+    printf("%d\n", cpm_fits(argc - 3, dims, size, atoi(argv[1]), atoi(argv[2])));
+    return 0;
+  }
   long plans = 0, bad = 0, streamed_ranges = 0;
   for (int d = 3; d <= 5; ++d) {
     // the plan depends on the two groups' products alone (and the largest mode): one shape for each pair
@@ -63,7 +71,7 @@ int main() {
         for (int k = 0; k < d; ++k) size *= dims[k];
         if (size < 512 || size > (1 << 17)) continue;
         for (int threads = 64; threads <= kCpmMaxThreads; threads += 64) {
-          if (!cpm_fits(d, dims, size, 1, threads)) continue;
+          if (!cpm_takes(d, dims, size, 1, threads)) continue;
           ++plans;
           const CpmPlan pl = cpm_plan(d, dims, threads);
           streamed_ranges += !pl.nr && pl.a.v.split > 1;

@@ -54,3 +54,18 @@ def test_streamed_ranges_at_thread_counts(dims, threads):
         assert abs(res[j] - oracle.cp_rel_residual(T.astype(np.float64), Bo)) <= tol
         for b, bo in zip(facs[j], Bo):
             assert rel_fro(host(b), bo) <= tol
+
+
+@pytest.mark.parametrize("dims,r", [((33, 33, 33), 3), ((40, 40, 40), 8), ((21, 38, 61), 10), ((21, 38, 61), 11),
+                                    ((9, 8, 8), 17), ((9, 8, 8), 23), ((2, 1, 51, 39), 8), ((7, 2, 53, 38), 3)])
+def test_either_side_of_the_lines_matches_oracle(dims, r):
+    """Shapes on both sides of the lines between this kernel and the one-contraction kernel."""
+    nnc = need_gpu()
+    T, (B0,), tol = _case(dims, [r])
+    Bo, _, _ = oracle.nncp(T.astype(np.float64), B0, 3)
+    B = [dev(b) for b in B0]
+    print("case", dims, r, flush=True)
+    res = nnc.nncp_fit(dev(T), r, 3, B)
+    for b, bo in zip(B, Bo):
+        assert rel_fro(host(b), bo) <= tol, (rel_fro(host(b), bo), tol)
+    assert abs(res - oracle.cp_rel_residual(T.astype(np.float64), Bo)) <= tol
