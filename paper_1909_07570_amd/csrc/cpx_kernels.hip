@@ -275,7 +275,9 @@ int64_t diag_part_floats(int64_t A, int64_t Nt, int64_t C, int r) {
 // B <- B * M / max(B H, eps) with M = sum_{s < slices} part[s] (s in order) and H = prod_{k != n} S_k
 // (entrywise, S packed [d][r][r]); FP64 division, clipped denominators counted.  Thread (row, rho),
 // 256 / r rows per block.  Bound by the latency of one round of loads: 4.8 us at 512 x 10 and 64 slices
-// (the sum and the update as two launches: 10.0).
+// (the sum and the update as two launches: 10.0).  kB slices are read together: as many as a few rounds
+// take, and one where there is only one (20 x 3: 0.8 us less than with 32 reads of it).
+template <int kB>
 __global__ __launch_bounds__(256) void cp_mu_k(float *__restrict__ B, const float *__restrict__ part, int slices,
                                                const float *__restrict__ S, int d, int n, int64_t N,
                                                int r, double eps, unsigned long long *clips) {
@@ -288,7 +290,7 @@ __global__ __launch_bounds__(256) void cp_mu_k(float *__restrict__ B, const floa
   const bool act = tid < rpb * r && i < N;
   // the loads of a group of slices are all in flight before the adds, the first group's (and the row's)
   // beside those of H; a slice past the last is read as the last and added as zero
-  constexpr int kB = 32, kR = 8;
+  constexpr int kR = 8;
   const int64_t n1 = N * r;
   const float *pe = part + (act ? i * r + q : 0);
   float v[kB], row[kR];
@@ -340,8 +342,16 @@ nnc_status launch_cp_mu(float *B, const float *part, int64_t slices, const float
                         double eps, unsigned long long *clips, hipStream_t s) {
   if (r < 1 || r > 32) return fail(NNC_EUNSUPPORTED, "rank %d outside [1, 32]", r);
   const int64_t rpb = 256 / r;
-  hipLaunchKernelGGL(cp_mu_k, dim3((unsigned)((N + rpb - 1) / rpb)), dim3(256), 0, s, B, part,
-                     (int)slices, S, d, n, N, r, eps, clips);
+#define NNC_CP_MU(KB)                                                                                            \
+  hipLaunchKernelGGL(cp_mu_k<KB>, dim3((unsigned)((N + rpb - 1) / rpb)), dim3(256), 0, s, B, part, (int)slices, S, d, n, \
+                     N, r, eps, clips)
+  if (slices == 1)
+    NNC_CP_MU(1);
+  else if (slices <= 8)
+    NNC_CP_MU(8);
+  else
+    NNC_CP_MU(32);
+#undef NNC_CP_MU
   NNC_HIP(hipGetLastError());
   return NNC_OK;
 }
