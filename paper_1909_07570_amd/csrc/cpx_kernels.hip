@@ -27,7 +27,7 @@ struct DiagArgs {
   int rho_first;
   float *out;  // [slices][Nt][r]
   int slices;
-  // block 0 forms the Gram gS = gB^T gB (gN x r) of another factor, if gB is not null
+  // block 0 of the kernels with a Gram (GRAM) forms gS = gB^T gB (gN x r) of another factor
   const float *gB;
   float *gS;
   int gN;
@@ -100,7 +100,7 @@ static __device__ inline void gram_sets(const float *__restrict__ B, int N, int 
 template <int RM>
 static __device__ inline bool diag_gram(const DiagArgs &g, float *part) {
   static_assert(kDiagThreads * RM >= kGramSums, "the Gram's sums fit the block's LDS");
-  if (!g.gB || blockIdx.x) return false;
+  if (blockIdx.x) return false;
   gram_sets<(RM + 15) / 16>(g.gB, g.gN, g.r, g.gS, part);
   return true;
 }
@@ -120,12 +120,13 @@ static __device__ inline float diag_w(const DiagArgs &g, int64_t a, int64_t c, i
 // (c fastest, contiguous in Y) and the partial sums are combined by a fixed pairwise tree
 // (thread t adds thread t + h for h = 128, 64, ..., 1).  The tree's two cross-wave steps
 // go through LDS; its steps inside wave 0 are shuffles that pair the same lanes.
-template <int RM>
+template <int RM, bool GRAM>
 __global__ __launch_bounds__(kDiagThreads) void diag_inner_k(DiagArgs g) {
   static_assert(kDiagThreads == 256, "the tree below has two cross-wave steps");
   __shared__ float red[kDiagThreads * RM];
-  if (diag_gram<RM>(g, red)) return;
-  const int t = threadIdx.x, block = blockIdx.x - (g.gB ? 1 : 0);
+  if constexpr (GRAM)
+    if (diag_gram<RM>(g, red)) return;
+  const int t = threadIdx.x, block = blockIdx.x - (GRAM ? 1 : 0);
   const int64_t i = block % g.Nt;
   const int s = (int)(block / g.Nt);
   const int64_t F = g.A * g.C;
@@ -172,11 +173,12 @@ __global__ __launch_bounds__(kDiagThreads) void diag_inner_k(DiagArgs g) {
 // ascending a); the rank index of a load is clamped instead of guarded, so no load waits on
 // a branch (accumulators past r are never stored), and lanes past Nt read row Nt - 1 and
 // are not stored either.
-template <int RM>
+template <int RM, bool GRAM>
 __global__ __launch_bounds__(kDiagThreads) void diag_outer_k(DiagArgs g) {
   __shared__ float red[kDiagThreads * RM];
-  if (diag_gram<RM>(g, red)) return;
-  const int block = blockIdx.x - (g.gB ? 1 : 0);
+  if constexpr (GRAM)
+    if (diag_gram<RM>(g, red)) return;
+  const int block = blockIdx.x - (GRAM ? 1 : 0);
   const int64_t tiles = (g.Nt + 63) / 64;
   const int64_t tile = block % tiles;
   const int s = (int)(block / tiles);
@@ -254,14 +256,22 @@ nnc_status launch_diag(const float *Y, int rho_first, int64_t A, int64_t Nt, int
   const int64_t blocks = (C > 1 ? Nt * S : ((Nt + 63) / 64) * S) + (gB ? 1 : 0);
   if (blocks > 0x7fffffff) return fail(NNC_EUNSUPPORTED, "diag: grid too large");
   const int RM = r <= 8 ? 8 : (r <= 16 ? 16 : 32);
-#define NNC_DIAG(KERN)                                                                         \
-  do {                                                                                         \
-    if (RM == 8) hipLaunchKernelGGL(KERN<8>, dim3((unsigned)blocks), dim3(kDiagThreads), 0, s, g);   \
-    else if (RM == 16) hipLaunchKernelGGL(KERN<16>, dim3((unsigned)blocks), dim3(kDiagThreads), 0, s, g); \
-    else hipLaunchKernelGGL(KERN<32>, dim3((unsigned)blocks), dim3(kDiagThreads), 0, s, g);          \
+#define NNC_DIAG2(KERN, GRAM)                                                                                        \
+  do {                                                                                                               \
+    if (RM == 8) hipLaunchKernelGGL((KERN<8, GRAM>), dim3((unsigned)blocks), dim3(kDiagThreads), 0, s, g);           \
+    else if (RM == 16) hipLaunchKernelGGL((KERN<16, GRAM>), dim3((unsigned)blocks), dim3(kDiagThreads), 0, s, g);    \
+    else hipLaunchKernelGGL((KERN<32, GRAM>), dim3((unsigned)blocks), dim3(kDiagThreads), 0, s, g);                  \
+  } while (0)
+#define NNC_DIAG(KERN)        \
+  do {                        \
+    if (gB)                   \
+      NNC_DIAG2(KERN, true);  \
+    else                      \
+      NNC_DIAG2(KERN, false); \
   } while (0)
   if (C > 1) NNC_DIAG(diag_inner_k);
   else NNC_DIAG(diag_outer_k);
+#undef NNC_DIAG2
 #undef NNC_DIAG
   NNC_HIP(hipGetLastError());
   return NNC_OK;
