@@ -814,6 +814,7 @@ __global__ __launch_bounds__(kNmfThreads) void nmf_mm_k(NmfArgs g) {
   float eps_up = (float)eps;  // den < eps in double if and only if den < eps_up: the float at or above it
   if ((double)eps_up < eps) eps_up = nextafterf(eps_up, INFINITY);
   const unsigned int lowest = __float_as_uint(fmaxf(eps_up, 1e-37f));  // and normal
+  const bool clip_all = eps_up > 3.4028234e38f;                        // no float is as large
   auto mu = [&](float x, float num, float den, bool valid) {
     const bool low = den < eps_up;
     mine += low && valid;
@@ -938,20 +939,25 @@ __global__ __launch_bounds__(kNmfThreads) void nmf_mm_k(NmfArgs g) {
           q_in[u] = 16 * (u >> 2) + li < m && rd + (u & 3) < N;
         }
         // All quotients of the lane at once, a step of every chain after the other (one by one they are a
-        // serial chain of ten FP64 operations each).  The reciprocal is the hardware's estimate and two
-        // Newton steps, within an ulp or two of double precision, so the float is the one of a division
-        // except where that lies within 2^-28 of its own rounding boundary; a division sequence takes 85
-        // cycles of a wave, this 21 (512 threads, eight independent quotients each).  Denominators to
-        // clip, subnormal, infinite or NaN take the division.
-        bool odd = false;
+        // serial chain of a dozen FP64 operations each).  The reciprocal is the hardware's estimate and two
+        // Newton steps, within an ulp or two of double precision, and the quotient is corrected by its
+        // remainder, which makes the float that of a division: the numerator is a product of two floats and
+        // the denominator a float, so a quotient that is not a rounding boundary of the floats (25 bits)
+        // itself lies at least 2^-49 of its size from it, and one that is comes out exact.  Denominators to
+        // clip, subnormal, infinite or NaN, and numerators that are infinite or NaN, take the division.
+        bool odd = clip_all;
+        double q_a[NQ];
 #pragma unroll
-        for (int u = 0; u < NQ; ++u) odd |= q_in[u] && __float_as_uint(q_den[u]) - lowest > 0x7f7fffffu - lowest;
+        for (int u = 0; u < NQ; ++u) {
+          q_a[u] = (double)q_x[u] * (double)q_num[u];
+          odd |= q_in[u] && (__float_as_uint(q_den[u]) - lowest > 0x7f7fffffu - lowest || !__builtin_isfinite(q_a[u]));
+        }
         float v[NQ];
         if (__any(odd)) {
 #pragma unroll
           for (int u = 0; u < NQ; ++u) v[u] = mu(q_x[u], q_num[u], q_den[u], q_in[u]);
         } else {
-          double q[NQ];
+          double q[NQ], t[NQ];
 #pragma unroll
           for (int u = 0; u < NQ; ++u) q[u] = __builtin_amdgcn_rcp((double)q_den[u]);
 #pragma unroll
@@ -959,7 +965,9 @@ __global__ __launch_bounds__(kNmfThreads) void nmf_mm_k(NmfArgs g) {
 #pragma unroll
             for (int u = 0; u < NQ; ++u) q[u] = fma(q[u], fma(-(double)q_den[u], q[u], 1.0), q[u]);
 #pragma unroll
-          for (int u = 0; u < NQ; ++u) v[u] = (float)(((double)q_x[u] * (double)q_num[u]) * q[u]);
+          for (int u = 0; u < NQ; ++u) t[u] = q_a[u] * q[u];
+#pragma unroll
+          for (int u = 0; u < NQ; ++u) v[u] = (float)fma(fma(-(double)q_den[u], t[u], q_a[u]), q[u], t[u]);
         }
         // rows past N may hold anything, ranks past m stay zero
 #pragma unroll
