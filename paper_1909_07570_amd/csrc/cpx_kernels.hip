@@ -12,6 +12,8 @@
 #include <string.h>
 
 #include <algorithm>
+#include <mutex>
+#include <set>
 
 #include "nnc_internal.h"
 
@@ -1104,9 +1106,32 @@ __global__ __launch_bounds__(kNmfThreads) void nmf_mm_k(NmfArgs g) {
   NNC_NMF(6, 2) NNC_NMF(6, 3) NNC_NMF(6, 4) NNC_NMF(6, 8)   \
   NNC_NMF(8, 2) NNC_NMF(8, 3) NNC_NMF(8, 4) NNC_NMF(8, 8)
 
+// Raises a kernel's dynamic-LDS limit to kNmfLdsMax, once.
+static nnc_status nmf_allow_lds(const void *kernel) {
+  static std::mutex mu;
+  static std::set<const void *> done;
+  std::lock_guard<std::mutex> lk(mu);
+  if (done.count(kernel)) return NNC_OK;
+  NNC_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kNmfLdsMax));
+  done.insert(kernel);
+  return NNC_OK;
+}
+
+// Few ranks over many rows, where a tile of 16 ranks is mostly padding and its waves' rounds over the
+// rows are what a sweep takes: nmf_block_k, a row a thread, gives the same bits sooner (us a sweep here
+// and there: 420 x 8 at m = 1 5.0 and 3.6, 512 x 2 at 4 5.5 and 4.6, 300 x 8 at 5 4.2 and 4.1; at up to
+// 128 rows, one round, 3.2 and 3.3 or more; 200 x 20 at 4 3.7 and 5.7).
+static bool nmf_block_sooner(const NmfArgs &g, int n, int mmax) {
+  int rows = 0;
+  for (int b = 0; b < n; ++b) rows = std::max(rows, g.rows[b]);
+  return (mmax <= 4 && rows > 128 && g.cols <= 16) || (mmax <= 6 && rows > 256 && g.cols <= 8);
+}
+
 // Launches the form that holds the largest rank and the columns; false where a problem's padded
-// layout does not fit the LDS (many rows), which nmf_block_k with its packed rows then takes.
+// layout does not fit the LDS (many rows), which nmf_block_k with its packed rows then takes, and
+// where that is the sooner one.
 static bool launch_nmf_mm(const NmfArgs &g, int n, int mmax, hipStream_t s, nnc_status *st) {
+  if (nmf_block_sooner(g, n, mmax)) return false;
   const int ms = mmax <= 16 ? 4 : mmax <= 20 ? 5 : mmax <= 24 ? 6 : 8;
   const int qs = g.cols <= 8 ? 2 : g.cols <= 12 ? 3 : g.cols <= 16 ? 4 : 8;
   size_t lds = 0;
@@ -1117,7 +1142,7 @@ static bool launch_nmf_mm(const NmfArgs &g, int n, int mmax, hipStream_t s, nnc_
 #undef NNC_NMF
   if (lds > kNmfLdsMax) return false;
   auto run = [&](auto *kernel) -> nnc_status {
-    NNC_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kNmfLdsMax));
+    NNC_TRY(nmf_allow_lds(reinterpret_cast<const void *>(kernel)));
     hipLaunchKernelGGL(kernel, dim3(n), dim3(kNmfThreads), lds, s, g);
     NNC_HIP(hipGetLastError());
     return NNC_OK;
@@ -1157,12 +1182,7 @@ nnc_status launch_nmf_block(int n, const float *const *A, const int *rows, int c
   const int RC = cols <= 8 ? 8 : (cols <= 16 ? 16 : 32), MC = mmax <= 8 ? 8 : (mmax <= 16 ? 16 : 32);
 #define NNC_NMF(RCV, MCV)                                                                         \
   do {                                                                                            \
-    static bool raised = false;                                                                   \
-    if (!raised) {                                                                                \
-      NNC_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(nmf_block_k<RCV, MCV>),          \
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)kNmfLdsMax)); \
-      raised = true;                                                                              \
-    }                                                                                             \
+    NNC_TRY(nmf_allow_lds(reinterpret_cast<const void *>(nmf_block_k<RCV, MCV>)));                \
     hipLaunchKernelGGL((nmf_block_k<RCV, MCV>), dim3(n), dim3(kNmfThreads), lds, s, g);           \
   } while (0)
 #define NNC_NMF_M(RCV)                \
