@@ -279,8 +279,9 @@ __global__ void contract_except_k(const float *__restrict__ U, const float *__re
 // eight waves one contiguous range each of the flattened summation index t = p * post + q, four
 // values of t a step; the waves' sums are added in order through LDS.  Every value is read straight
 // into the layout of the products, eight steps' loads together, so a block costs about two memory
-// round trips (512 rows, t < 400, J = 20: 8.1 us; a wave per row with V in LDS and a butterfly per
-// column: 17.5 us).  Sums of at most total / 8 products run in order, the rest as a tree's.
+// round trips (512 rows, t < 400, J = 20: 8.6 us; a wave per row with V in LDS and a butterfly per
+// column: 17.5 us).  The eight steps of a round have an accumulator each, so a 64th of the products
+// runs in order and the rest as a tree, as with a wave per row.
 constexpr int kCeWaves = 8;
 
 template <int RT>
@@ -299,12 +300,12 @@ __global__ __launch_bounds__(64 * kCeWaves) void contract_except_rows_k(const fl
   int jc[RT];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) jc[rt] = min(16 * rt + li, J - 1);
-  f4 acc[2][RT];  // by step parity: independent chains
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) acc[a][rt] = f4{0.f, 0.f, 0.f, 0.f};
   constexpr int kS = 8;
+  f4 acc[kS][RT];
+#pragma unroll
+  for (int k = 0; k < kS; ++k)
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) acc[k][rt] = f4{0.f, 0.f, 0.f, 0.f};
   for (int s0 = wave * per; s0 < s1; s0 += kS) {
     float u[kS], v[kS][RT];
 #pragma unroll
@@ -325,15 +326,23 @@ __global__ __launch_bounds__(64 * kCeWaves) void contract_except_rows_k(const fl
     for (int k = 0; k < kS; ++k)
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt)
-        acc[k & 1][rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(u[k], v[k][rt], acc[k & 1][rt], 0, 0, 0);
+        acc[k][rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(u[k], v[k][rt], acc[k][rt], 0, 0, 0);
   }
+  auto tree = [](const f4 (&x)[8]) { return ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7])); };
+  static_assert(kS == 8 && kCeWaves == 8, "the trees below");
 #pragma unroll
-  for (int rt = 0; rt < RT; ++rt) part[wave][rt][lane] = acc[0][rt] + acc[1][rt];
+  for (int rt = 0; rt < RT; ++rt) {
+    f4 x[kS];
+#pragma unroll
+    for (int k = 0; k < kS; ++k) x[k] = acc[k][rt];
+    part[wave][rt][lane] = tree(x);
+  }
   __syncthreads();
   if (wave >= RT) return;
-  f4 sum = f4{0.f, 0.f, 0.f, 0.f};
+  f4 x[kCeWaves];
 #pragma unroll
-  for (int w = 0; w < kCeWaves; ++w) sum += part[w][wave][lane];
+  for (int w = 0; w < kCeWaves; ++w) x[w] = part[w][wave][lane];
+  const f4 sum = tree(x);
   const int j = 16 * wave + li;
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
