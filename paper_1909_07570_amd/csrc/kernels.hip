@@ -284,7 +284,7 @@ __global__ void contract_except_k(const float *__restrict__ U, const float *__re
 // runs in order and the rest as a tree, as with a wave per row.
 constexpr int kCeWaves = 8;
 
-template <int RT>
+template <int RT, bool LONG>  // LONG: sums of 2^22 products and more, whose indices need the integer division
 __global__ __launch_bounds__(64 * kCeWaves) void contract_except_rows_k(const float *__restrict__ U,
                                                                         const float *__restrict__ V, int pre,
                                                                         int64_t I, int J, int post,
@@ -312,7 +312,7 @@ __global__ __launch_bounds__(64 * kCeWaves) void contract_except_rows_k(const fl
     for (int k = 0; k < kS; ++k) {
       const int t = 4 * (s0 + k) + lg;
       const bool ok = s0 + k < s1 && t < total;
-      const int tt = ok ? t : 0, p = qdiv(tt, inv_post), q = tt - p * post;
+      const int tt = ok ? t : 0, p = LONG ? tt / post : qdiv(tt, inv_post), q = tt - p * post;
       u[k] = U[((int64_t)p * I + ir) * post + q];
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) v[k][rt] = V[(p * J + jc[rt]) * post + q];
@@ -425,14 +425,22 @@ nnc_status launch_contract_except(const float *U, const float *V, int64_t pre, i
     NNC_HIP(hipGetLastError());
     return NNC_OK;
   }
-  if (J <= 32 && pre * J * post < INT32_MAX && pre * post < (1 << 22) && I < ((int64_t)1 << 31) / 64) {
+  if (J <= 32 && pre * J * post < INT32_MAX && I < ((int64_t)1 << 31) / 64) {
     const int grid = (int)((I + 15) / 16);
-    if (J <= 16)
-      hipLaunchKernelGGL(contract_except_rows_k<1>, dim3(grid), dim3(64 * kCeWaves), 0, s, U, V, (int)pre, I, (int)J,
-                         (int)post, out);
-    else
-      hipLaunchKernelGGL(contract_except_rows_k<2>, dim3(grid), dim3(64 * kCeWaves), 0, s, U, V, (int)pre, I, (int)J,
-                         (int)post, out);
+#define NNC_CE_ROWS(RT, LONG)                                                                              \
+  hipLaunchKernelGGL((contract_except_rows_k<RT, LONG>), dim3(grid), dim3(64 * kCeWaves), 0, s, U, V, (int)pre, I, \
+                     (int)J, (int)post, out)
+    if (pre * post < (1 << 22)) {
+      if (J <= 16)
+        NNC_CE_ROWS(1, false);
+      else
+        NNC_CE_ROWS(2, false);
+    } else if (J <= 16) {
+      NNC_CE_ROWS(1, true);
+    } else {
+      NNC_CE_ROWS(2, true);
+    }
+#undef NNC_CE_ROWS
     NNC_HIP(hipGetLastError());
     return NNC_OK;
   }

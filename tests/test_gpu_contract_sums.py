@@ -31,3 +31,20 @@ def test_a_large_product_loses_few_of_the_others(r0, r1, r2, n0):
     off = (-g[0].double() - (big + total - 1)).abs()
     # the chain, a tree of eight of them and a tree of the eight waves' sums
     assert off.max().item() <= chain + 6, (off.max().item(), chain)
+
+
+@pytest.mark.parametrize("r0", [2, 17])
+def test_sums_of_more_than_two_to_the_22_products(r0):
+    """The same over 33 x 50 x 50 x 52 products, past the indices that a float division splits."""
+    nnc = need_gpu()
+    n0, rest = 65, (33, 50, 50, 52)
+    total = int(np.prod(rest))
+    chain = 4 * -(-(-(-(-(-total // 4)) // 8)) // 8)
+    X = torch.ones(n0, *rest, device="cuda")
+    at = np.linspace(0, total - 1, n0).astype(int)
+    X.view(n0, total)[torch.arange(n0), torch.from_numpy(at)] = 2.0 ** 24
+    G = torch.ones(r0, *rest, device="cuda")
+    print("case", r0, flush=True)
+    _, _, g = nnc.nntucker_grad(X, G, [torch.zeros(n0, r0, device="cuda")] + [torch.eye(n, device="cuda") for n in rest])
+    off = (-g[0].double() - (2.0 ** 24 + total - 1)).abs()
+    assert off.max().item() <= chain + 6, (off.max().item(), chain)
