@@ -370,14 +370,14 @@ __global__ __launch_bounds__(64 * kCpmWaves) void nncp_mm_k(const float *__restr
       *reinterpret_cast<f4 *>(Hp + (e + lane) * 4) = h;
     }
   };
-  // the ranges that M_n's sum is split into: the waves but the two with a Gram and H to form
+  // (by the rank, not RS, which depends on the launch's other fits)
   auto m_split = [&](int In, int terms) {
-    // (by the rank, not RS, which depends on the launch's other fits)
-    const int n = qdiv(64 * max(nw - 2, 1), 1.0f / (float)(In * nq));
-    return max(1, min(n, min(terms, 16)));
+    return cpm_sum_ranges(qdiv(64 * max(nw - 2, 1), 1.0f / (float)(In * nq)), terms);
   };
   // M_n's partial sums from V or U (rows: the group F .. L, row-major, `split` ranges to add), four
-  // ranks a thread.  Bo: the sweep's old factors, Bn: its new ones.
+  // ranks a thread, in rows of the fit's own quads (ps floats: m_split's ranges then stay within part
+  // whatever the launch's largest rank).  Bo: the sweep's old factors, Bn: its new ones.
+  const int ps = 4 * nq;
   auto m_part = [&](auto N, auto F, auto L, const float *Bo, const float *Bn, int rows, int split) {
     // the group's other modes: xm (if there are two) outside ym
     constexpr int n = N, o1 = F != N ? int(F) : F + 1, o2 = o1 + 1 != N ? o1 + 1 : o1 + 2;
@@ -414,13 +414,13 @@ __global__ __launch_bounds__(64 * kCpmWaves) void nncp_mm_k(const float *__restr
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[j] = fmaf(v[j], by[j], acc[j]);
       }
-      *reinterpret_cast<f4 *>(part + (s * In + i) * RS + c) = acc;
+      *reinterpret_cast<f4 *>(part + (s * In + i) * ps + c) = acc;
     }
   };
   // B_n <- B_n * M / max(B_n H, eps) into the other buffer, one value a thread (B_n H on the
   // matrix cores, four values a lane, was 60 to 150 % slower: longer chains on fewer waves); M:
-  // `split` arrays of In x RS.  H is symmetric, so its row c is read for column c.
-  auto update = [&](auto N, const float *M, int split, const float *Bo, float *Bn) {
+  // `split` arrays of In rows, `ms` floats apart.  H is symmetric, so its row c is read for column c.
+  auto update = [&](auto N, const float *M, int split, int ms, const float *Bo, float *Bn) {
     constexpr int n = N, pv = (N + D - 1) % D;
     const int In = a.dims[n];
     const float *B = Bo + off[n];
@@ -438,7 +438,7 @@ __global__ __launch_bounds__(64 * kCpmWaves) void nncp_mm_k(const float *__restr
       }
       float m = 0.f;
 #pragma unroll 4
-      for (int q = 0; q < split; ++q) m += M[q * In * RS + e];
+      for (int q = 0; q < split; ++q) m += M[(q * In + i) * ms + c];
       double den = (double)((d4[0] + d4[1]) + (d4[2] + d4[3]));
       if (den < eps) {
         den = eps;
@@ -462,11 +462,11 @@ __global__ __launch_bounds__(64 * kCpmWaves) void nncp_mm_k(const float *__restr
         m_part(N, F, L, Bo, Bn, rows, split);
         __syncthreads();
         constexpr int o1 = F != N ? int(F) : F + 1, o2 = o1 + 1 != N ? o1 + 1 : o1 + 2;
-        update(N, part, m_split(a.dims[N], o2 <= L ? a.dims[o1] * a.dims[o2 <= L ? o2 : 0] : a.dims[o1]), Bo, Bn);
+        update(N, part, m_split(a.dims[N], o2 <= L ? a.dims[o1] * a.dims[o2 <= L ? o2 : 0] : a.dims[o1]), ps, Bo, Bn);
         __syncthreads();
       };
       if constexpr (F == L) {
-        update(F, VU, split, Bo, Bn);
+        update(F, VU, split, RS, Bo, Bn);
         __syncthreads();
       } else {
         mode(F);

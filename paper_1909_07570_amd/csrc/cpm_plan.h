@@ -106,13 +106,22 @@ inline CpmPlan cpm_plan(int d, const int64_t *dims, int threads) {
 
 // Rows of every array over ranks hold RS = 8, 16 or 32 values, zeros past the rank.  LDS floats of
 // a fit with `threads` threads:
-//   factors, two buffers | Grams (d RS WS) | H (RS WS) | partial sums of M_n (or, with one mode
-//   in a group, none) | KR of the left group | KR of the right group (groups of one mode are the
+//   factors, two buffers | Grams (d RS WS) | H (RS WS) | partial sums of M_n (cpm_sum_ranges times In
+//   rows of the fit's quads; or, with one mode in a group, none) | KR of the left group | KR of the right group (groups of one mode are the
 //   factor itself) | V or U, by ranges of the contracted index.  The residual's FP64 sums reuse
 //   V and U, which are at least 4 floats a thread.
 // Rows of the Grams and of H are WS = RS + 4 floats apart: an update reads 16 of them at once, 16
 // bytes each, from 64 different banks.  All of it starts as zeros: operand reads past an array's
 // last row meet zeros of T, and have to be finite.
+// The ranges that M_n's sum over `terms` terms is split into, by the fit's own rank (nq quads) alone: the
+// threads of the waves but the two with a Gram and H to form, each with a quad of a row.  In times the
+// ranges is at most 64 max(nw - 2, 1) / nq, or In where that is less than one range: at most 4 * threads
+// or maxdim * RS floats of sums.
+NNC_HD inline int cpm_sum_ranges(int per, int terms) {
+  const int most = terms < 16 ? terms : 16, n = per < most ? per : most;
+  return n > 1 ? n : 1;
+}
+
 inline int cpm_rs(int r) { return r <= 8 ? 8 : (r <= 16 ? 16 : 32); }
 
 inline int64_t cpm_lds_floats(const CpmArgs &a, int RS, int threads) {

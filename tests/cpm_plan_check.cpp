@@ -1,6 +1,7 @@
 // Walks the launch plan of the matrix-core nnCP kernel (cpm_plan.h) as the kernel's waves do, for every
 // shape and thread count that it takes, and counts how often each unit (16-row tile and range of the
-// contracted index) of the two products comes up: exactly once, within the registers of the variant.
+// contracted index) of the two products comes up: exactly once, within the registers of the variant.  The
+// partial sums of the updates stay within their LDS.
 // Prints the number of plans and the first shapes that fail; the exit status is 1 if any does.
 // With arguments (rank, threads, modes): whether the kernel is the one that such a fit goes to.
 #include <cstdio>
@@ -31,6 +32,20 @@ static bool once(const CpmProd &p, int ks, int nw, int nr) {
   return true;
 }
 
+// The partial sums of every M_n, for every rank of a fit, stay within their region of the LDS.
+static bool sums_fit(const CpmArgs &a, int threads) {
+  const int nw = threads / 64;
+  for (int RS : {8, 16, 32})
+    for (int nq = 1; 4 * nq <= RS; ++nq)
+      for (int n = 0; n < a.d; ++n) {
+        const int group = n < a.s ? a.pL : a.pR;
+        if ((n < a.s ? a.s : a.d - a.s) == 1) continue;
+        const int In = a.dims[n], per = 64 * std::max(nw - 2, 1) / (In * nq);
+        if ((int64_t)In * cpm_sum_ranges(per, group / In) * 4 * nq > std::max(4 * threads, a.maxdim * RS)) return false;
+      }
+  return true;
+}
+
 static bool plan_ok(int d, const int64_t *dims, int threads) {
   const CpmPlan pl = cpm_plan(d, dims, threads);
   const CpmArgs &a = pl.a;
@@ -38,7 +53,7 @@ static bool plan_ok(int d, const int64_t *dims, int threads) {
   const bool v = pl.ns == 8   ? pl.nr == 64 && once<8>(a.v, a.pR, nw, pl.nr)
                  : pl.ns == 4 ? once<4>(a.v, a.pR, nw, pl.nr)
                               : pl.ns == 1 && once<1>(a.v, a.pR, nw, pl.nr);
-  return v && once<1>(a.u, a.pL, nw, pl.nr);
+  return v && once<1>(a.u, a.pL, nw, pl.nr) && sums_fit(a, threads);
 }
 
 int main(int argc, char **argv) {
