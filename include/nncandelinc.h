@@ -127,8 +127,8 @@ nnc_status nnc_ttm(const void *X, nnc_dtype xdt, int ndim, const int64_t *dims, 
 /* The kernel the calling thread's last nnc_ttm launched: "ttm_last_lds_bf16",
  * "ttm_mid_f32", ... for the matrix-core X-streaming kernels ("(chunked)" when the contracted
  * index was split into several launches, "(ragged)" when rows do not start at 16-byte
- * boundaries), "ttm_generic" for the general kernel.  A static
- * string, never NULL. */
+ * boundaries, "(ragged, chunked)" when both hold), "ttm_generic" for the general kernel.  A
+ * static string, never NULL. */
 const char *nnc_last_ttm_kernel(void);
 
 /* Round FP32 to bfloat16 (round to nearest, ties to even; NaN stays NaN).  out holds

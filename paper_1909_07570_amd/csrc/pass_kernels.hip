@@ -1088,7 +1088,10 @@ nnc_status launch_pass(const void *X, nnc_dtype xdt, int64_t P, int64_t N, int64
           NNC_TRY(launch_last_lds(static_cast<const char *>(X) + k0 * esz, bf, P, kc, F + k0 * ldl, ldl, ldr, R,
                                   out, s, nullptr, reserve_cus, N, c > 0, rag));
         }
-        if (kernel_name) *kernel_name = bf ? "ttm_last_lds_bf16 (chunked)" : "ttm_last_lds_f32 (chunked)";
+        if (kernel_name && rag)
+          *kernel_name = bf ? "ttm_last_lds_bf16 (ragged, chunked)" : "ttm_last_lds_f32 (ragged, chunked)";
+        else if (kernel_name)
+          *kernel_name = bf ? "ttm_last_lds_bf16 (chunked)" : "ttm_last_lds_f32 (chunked)";
         return NNC_OK;
       }
     }
@@ -1166,7 +1169,8 @@ nnc_status launch_pass(const void *X, nnc_dtype xdt, int64_t P, int64_t N, int64
 #undef NNC_MID
     }
     if (kernel_name && rag)
-      *kernel_name = bf ? "ttm_mid_bf16 (ragged)" : "ttm_mid_f32 (ragged)";
+      *kernel_name = Nc < N ? (bf ? "ttm_mid_bf16 (ragged, chunked)" : "ttm_mid_f32 (ragged, chunked)")
+                            : (bf ? "ttm_mid_bf16 (ragged)" : "ttm_mid_f32 (ragged)");
     else if (kernel_name)
       *kernel_name = Nc < N ? (bf ? "ttm_mid_bf16 (chunked)" : "ttm_mid_f32 (chunked)") : (bf ? "ttm_mid_bf16" : "ttm_mid_f32");
   }
