@@ -672,10 +672,14 @@ struct ResidChain {
   }
 };
 
+// Waves per SIMD: 16 rows in flight (NS 1, and BF16) and the factor's values in 128 registers up to 16
+// ranks or 32 values a lane, else in 168.
+static constexpr int resid_waves(int rb, int ns) { return rb * ns > 32 || (ns == 1 && rb > 16) ? 3 : 4; }
+
 // nst stripes; the grid's waves take stripe gw % nst and row tiles gw / nst, + rstep, ...
 // of kRows rows, or, with more stripes than waves, stripes gw, gw + sstep, ... and every row.
 template <typename XT, int RB, int NS>
-__global__ __launch_bounds__(kResidThreads) __attribute__((amdgpu_waves_per_eu(RB * NS > 32 ? 3 : 4))) void resid_stream_k(
+__global__ __launch_bounds__(kResidThreads) __attribute__((amdgpu_waves_per_eu(resid_waves(RB, NS)))) void resid_stream_k(
     const XT *__restrict__ X, int64_t M, int64_t K, const float *__restrict__ W, const float *__restrict__ Ad, int R,
     double *__restrict__ part, int64_t nst, int64_t sstep, int64_t rstep) {
   __shared__ double s0[kResidThreads], s1[kResidThreads];
@@ -855,9 +859,8 @@ nnc_status launch_resid_stream(const void *X, nnc_dtype xdt, int64_t M, int64_t 
   const int NS = K >= 2 && (half % 2 == 0 || half > 8) ? 2 : 1;
   const int rows = xdt == NNC_F32 && NS == 2 ? 8 : 16;  // the kernel's kRows
   const int64_t ntile = (M + rows - 1) / rows, nst = NS == 2 ? (half + 1) / 2 : half;
-  // as many waves as reside together (four per SIMD on 256 CUs, three with more than 32 factor
-  // values a lane): one round of equal shares
-  const int64_t most = (R + 3) / 4 * 4 * NS > 32 ? 768 : 1024;
+  // as many waves as reside together: one round of equal shares (a CU has four SIMDs, a block four waves)
+  const int64_t most = std::min<int64_t>((int64_t)device_cu_count() * resid_waves((int)(R + 3) / 4 * 4, NS), kResidMaxBlocks);
   const int grid = (int)std::min<int64_t>((ntile * nst + kResidWaves - 1) / kResidWaves, most);
   const int64_t waves = (int64_t)grid * kResidWaves;
   const int64_t rstep = nst <= waves ? waves / nst : 1, sstep = waves;
