@@ -39,26 +39,6 @@ constexpr int kLsSplit = 32;      // row ranges of Z at most
 
 typedef double d2 __attribute__((ext_vector_type(2)));
 
-// dst[e] = src[e] for e < n by the whole block, eight independent loads in flight per
-// thread before their stores (a loop that stores each load before issuing the next waits a
-// full memory round trip per element).
-template <typename D>
-__device__ inline void block_copy(const float *__restrict__ src, D *__restrict__ dst, int n) {
-  for (int e0 = threadIdx.x; e0 < n; e0 += 8 * blockDim.x) {
-    float v[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int e = e0 + k * blockDim.x;
-      v[k] = e < n ? src[e] : 0.f;
-    }
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int e = e0 + k * blockDim.x;
-      if (e < n) dst[e] = (D)v[k];
-    }
-  }
-}
-
 // 1 / x and 1 / sqrt(x) by the hardware's estimates and two Newton steps (an ulp or two of double).
 __device__ inline double rcp_d(double x) {
   double r = __builtin_amdgcn_rcp(x);

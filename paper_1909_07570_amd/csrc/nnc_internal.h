@@ -272,7 +272,6 @@ nnc_status launch_core_last(const CoreArgsHost &h, hipStream_t s);
 nnc_status launch_small_with_core(const float *in, int64_t P, int64_t N, int64_t Q, const float *F,
                                   int64_t ldl, int64_t ldr, int64_t R, float *out,
                                   const CoreArgsHost &h, hipStream_t s);
-// out[e] = sum_{b < nparts} part[b][e] (fixed order)
 // Nonnegative CP of the data tensor (cpx_kernels.hip).
 // launch_diag: part <- the diag_slices(A, Nt, C) partial sums [Nt][r] of M, and in the same launch the
 // Gram gS = gB^T gB where gB is not null (diag_gram_fits(gN, r)); launch_cp_mu adds the slices.

@@ -151,17 +151,6 @@ static __device__ inline float tiny_contract_except(const TinyCtx &c, const floa
   return s;
 }
 
-// Entry (i, b) of A Mm for the symmetric Mm, K columns.
-template <int K>
-static __device__ inline float tiny_den(const TinyCtx &c, const float *A, const float *Mm) {
-  float x[K], m[K], s = 0.f;
-  tiny_row<K>(A + c.row * 8, x);
-  tiny_row<K>(Mm + c.col * 8, m);
-#pragma unroll
-  for (int k = 0; k < K; ++k) s = fmaf(x[k], m[k], s);
-  return s;
-}
-
 // Mode NM of a sweep of the blockwise nnTucker rule.
 template <int NM, int KN, int KM>
 static __device__ inline void tiny_tucker_mode(TinyCtx &c, TinyLds &L, const int *N, const int *M) {
