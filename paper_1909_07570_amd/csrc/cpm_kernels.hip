@@ -23,11 +23,12 @@
 //     last Gram in.
 // Sums run in a fixed order: results are reproducible and do not depend on what else is launched.
 //
-// Measured, us a sweep (nncp_k in brackets): 8^5 at rank 16 12.4 (158), 24^3 at rank 16 7.7, 20^3
-// at rank 10 5.7 (8.5), 10 x 10 x 11 x 10 at rank 8 6.4 and 12^3 at rank 6 3.9.  The two products of 8^5 take 6.0 and 5.2 thousand of its 30 thousand cycles (4.1
-// each is what the matrix cores need); the rest is twelve phases of 0.7 to 2.3 thousand, chains of
-// a few LDS round trips and, in the updates, an FP64 division.  Sixteen waves were slower: every
-// instruction of a phase then issues four times per SIMD.
+// Measured, us a sweep (nncp_k in brackets): 8^5 at rank 16 12.4 (155), 24^3 at rank 16 7.7 (11.8), 20^3
+// at rank 10 5.8 (8.3), 10 x 10 x 11 x 10 at rank 8 6.5 (27), 4 x 8 x 12 x 16 at rank 10 8.3 (23) and 12^3
+// at rank 6 4.0 (5.2); a call adds 60 to 90 us.  The two products of 8^5 take 6.0 and 5.2 thousand of
+// its 30 thousand cycles (4.1 each is what the matrix cores need); the rest is twelve phases of 0.7 to
+// 2.3 thousand, chains of a few LDS round trips and, in the updates, an FP64 division.  Sixteen waves
+// were slower: every instruction of a phase then issues four times per SIMD.
 #include <map>
 #include <mutex>
 

@@ -756,8 +756,8 @@ __global__ __launch_bounds__(kNmfThreads) void nmf_block_k(NmfArgs g) {
 // bit for bit (the iteration is not contracting: another order moves the result of a few hundred
 // sweeps by more than rounding).  One quad of ranks past a multiple of 16 (m = 17 .. 20) has its
 // part of the W step on the VALU, a value a lane, instead of a second tile of three quarters zeros.
-// Bound: instruction issue and latency in one CU: three 512 x 10 at m = 20, 8.7 us a sweep in this
-// form, 26.5 in nmf_block_k.
+// Bound: instruction issue and latency in one CU: three 512 x 10 at m = 20, 8.4 us a sweep in this
+// form, 26.2 in nmf_block_k.
 // =====================================================================================
 constexpr int kNmfWaves = kNmfThreads / 64;
 

@@ -119,7 +119,7 @@ nnc_status launch_ttm(const void *X, nnc_dtype xdt, int64_t P, int64_t N, int64_
 //                    the factor row of its (n, q .. q + V - 1) and walks p, whose R x Q inputs
 //                    pass through LDS a few p at a time.
 // Measured (in brackets: the general contraction kernel, one thread per output column walking
-// n): 64^4 x 8 from 64^3 x 8 x 8 125 us (560), 128^3 x 16 36 us (230), 256^2 x 32 12 us (26).
+// n): 64^4 x 8 from 64^3 x 8 x 8 111 us (560), 128^3 x 16 37 us (230), 256^2 x 32 16 us (26).
 // The line between the two is where a row of q fills a block.
 // =====================================================================================
 template <int V>

@@ -23,7 +23,7 @@
 // Cholesky factor and its inverse are one wave's too; lanes' values go through scalar registers.
 // 512 x 20: 24 us (27 through LDS), with 256 threads and a barrier for each pivot and column 64 us.
 // ls_apply_k takes 6.0 us where rows, rotation and copy took 17.7, ls_inv_k 8.9 (34 for the modes in
-// turn).  Ten sweeps at 512^3, R = 20 (two on FP32 X), whole fit: 3.64 ms (6.11).
+// turn).  Ten sweeps at 512^3, R = 20 (two on FP32 X), whole fit: 3.67 ms (6.11).
 #include <algorithm>
 #include <mutex>
 
